@@ -1,5 +1,5 @@
 // Layer epilogue: y = x + sum over K-slices of the down projection's partials, then (inside a stack) the next
-// layer's FFN input xn = y * g in the FFN kernels' input dtype and the row's partial sums of squares, from which
+// layer's FFN input xn = y * g in bf16 and the row's partial sums of squares, from which
 // the next gate/up kernel forms the RMSNorm factor 1 / sqrt(mean(y^2) + eps).
 //
 // One wave per (token row, block of 256 columns), each lane a float4, so the launch has B T d / 256 waves.  The
@@ -20,11 +20,10 @@ __device__ __forceinline__ float4 add4(float4 a, float4 b) {
 
 __device__ __forceinline__ float4 ld4(const float *p) { return *reinterpret_cast<const float4 *>(p); }
 
-template <bool kBf16Xn>
 __global__ __launch_bounds__(kThreads) void epilogue_kernel(const float *__restrict__ part, int slices,
                                                             int slice_neurons, const int32_t *__restrict__ count,
                                                             int max_count, const float *x, float *y, int T, int d,
-                                                            int nblk, void *__restrict__ xn_next,
+                                                            int nblk, uint16_t *__restrict__ xn_next,
                                                             const float *__restrict__ g_next,
                                                             float *__restrict__ ssq, const float *__restrict__ ya_in,
                                                             float *__restrict__ ya_out,
@@ -100,14 +99,10 @@ __global__ __launch_bounds__(kThreads) void epilogue_kernel(const float *__restr
         }
     }
     if (!ok) return;
-    if constexpr (kBf16Xn) {
-        uint2 packed;
-        packed.x = rm_f32_to_bf16_bits(out.x) | (rm_f32_to_bf16_bits(out.y) << 16);
-        packed.y = rm_f32_to_bf16_bits(out.z) | (rm_f32_to_bf16_bits(out.w) << 16);
-        *reinterpret_cast<uint2 *>(static_cast<uint16_t *>(xn_next) + ro) = packed;
-    } else {
-        *reinterpret_cast<float4 *>(static_cast<float *>(xn_next) + ro) = out;
-    }
+    uint2 packed;
+    packed.x = rm_f32_to_bf16_bits(out.x) | (rm_f32_to_bf16_bits(out.y) << 16);
+    packed.y = rm_f32_to_bf16_bits(out.z) | (rm_f32_to_bf16_bits(out.w) << 16);
+    *reinterpret_cast<uint2 *>(xn_next + ro) = packed;
 }
 
 }  // namespace
@@ -119,18 +114,14 @@ hipError_t launch_epilogue(const Plan &p, const int32_t *count, const float *x, 
                            hipStream_t st) {
     char *base = static_cast<char *>(ws);
     const float *part = reinterpret_cast<const float *>(base + p.off_part);
-    void *xn = emit_xn ? static_cast<void *>(base + p.off_xn) : nullptr;
+    uint16_t *xn = emit_xn ? reinterpret_cast<uint16_t *>(base + p.off_xn) : nullptr;  // bf16 calls only
     float *ssq = reinterpret_cast<float *>(base + p.off_ssq);
     const int nblk = (p.d + kRowBlock - 1) / kRowBlock;
     const dim3 grid(p.B * p.T * nblk);
     const int slice_neurons = p.wdtype == RM_BF16 ? p.slice_units * kBfChunk : p.slice_units;
     const float *g = emit_xn ? g_next : nullptr;
-    if (p.wdtype == RM_BF16)
-        hipLaunchKernelGGL(epilogue_kernel<true>, grid, dim3(kThreads), 0, st, part, p.slices, slice_neurons, count,
-                           p.max_count, x, y, p.T, p.d, nblk, xn, g, ssq, ya_in, ya_out, out_gate);
-    else
-        hipLaunchKernelGGL(epilogue_kernel<false>, grid, dim3(kThreads), 0, st, part, p.slices, slice_neurons,
-                           count, p.max_count, x, y, p.T, p.d, nblk, xn, g, ssq, ya_in, ya_out, out_gate);
+    hipLaunchKernelGGL(epilogue_kernel, grid, dim3(kThreads), 0, st, part, p.slices, slice_neurons, count,
+                       p.max_count, x, y, p.T, p.d, nblk, xn, g, ssq, ya_in, ya_out, out_gate);
     return hipGetLastError();
 }
 

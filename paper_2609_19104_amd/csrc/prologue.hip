@@ -1,5 +1,5 @@
-// First layer's FFN input: xn = x * g (or x without a norm) in the FFN kernels' input dtype, plus the row's
-// sums of squares for the RMSNorm factor.  Also the identity index lists with which the dense reference runs the
+// First layer's FFN input of the bf16 kernels: xn = x * g (or x without a norm) in bf16, plus the row's sums of
+// squares for the RMSNorm factor.  Also the identity index lists with which the dense reference runs the
 // sparse kernels, and the launch that runs the mask compaction beside the prologue (the calls that take masks).
 //
 // The action expert normalizes each FFN input (the layer is x + FFN(RMSNorm(x)) with RMSNorm(x) =
@@ -15,20 +15,18 @@ namespace {
 
 constexpr int kThreads = 64;
 
-template <bool kBf16Out>
 __global__ __launch_bounds__(kThreads) void prologue_kernel(const float *__restrict__ x,
                                                             const float *__restrict__ g, int d, int nblk,
-                                                            void *__restrict__ xn, float *__restrict__ ssq) {
-    rm_units::prologue_unit<kBf16Out>(x, g, d, nblk, xn, ssq, blockIdx.x, threadIdx.x);
+                                                            uint16_t *__restrict__ xn, float *__restrict__ ssq) {
+    rm_units::prologue_unit(x, g, d, nblk, xn, ssq, blockIdx.x, threadIdx.x);
 }
 
 // Compaction and prologue in one launch (they are independent): workgroups [0, n_compact) each compact one
 // (mask, segment) unit; each later workgroup runs the prologue of four (row, column block) units, one per wave.
-template <bool kBf16Out>
 __global__ __launch_bounds__(rm_units::kCompactThreads) void compact_prologue_kernel(
     const uint8_t *__restrict__ mask, int d_ff, int nseg, int n_compact, int32_t *__restrict__ idx,
     int32_t *__restrict__ count, const float *__restrict__ x, const float *__restrict__ g, int d, int nblk,
-    int units, void *__restrict__ xn, float *__restrict__ ssq) {
+    int units, uint16_t *__restrict__ xn, float *__restrict__ ssq) {
     const int w = static_cast<int>(blockIdx.x);
     if (w < n_compact) {
         const int m = w / nseg;
@@ -36,7 +34,7 @@ __global__ __launch_bounds__(rm_units::kCompactThreads) void compact_prologue_ke
         return;
     }
     const int unit = (w - n_compact) * (rm_units::kCompactThreads / 64) + static_cast<int>(threadIdx.x >> 6);
-    if (unit < units) rm_units::prologue_unit<kBf16Out>(x, g, d, nblk, xn, ssq, unit, threadIdx.x & 63);
+    if (unit < units) rm_units::prologue_unit(x, g, d, nblk, xn, ssq, unit, threadIdx.x & 63);
 }
 
 __global__ __launch_bounds__(256) void identity_lists_kernel(int32_t *idx, int32_t *count, int d_ff, int B) {
@@ -64,7 +62,7 @@ hipError_t launch_identity_lists(const Plan &p, void *ws, hipStream_t st) {
 hipError_t launch_compact_prologue(const Plan &p, const uint8_t *mask, int n_masks, int32_t *idx, int32_t *count,
                                    const float *x, const float *norm_g, void *ws, hipStream_t st) {
     char *base = static_cast<char *>(ws);
-    void *xn = base + p.off_xn;
+    uint16_t *xn = reinterpret_cast<uint16_t *>(base + p.off_xn);
     float *ssq = reinterpret_cast<float *>(base + p.off_ssq);
     const int nblk = (p.d + kRowBlock - 1) / kRowBlock;
     const int nseg = (p.d_ff + rm_units::kSeg - 1) / rm_units::kSeg;
@@ -73,25 +71,18 @@ hipError_t launch_compact_prologue(const Plan &p, const uint8_t *mask, int n_mas
     const int per = rm_units::kCompactThreads / 64;
     const dim3 grid(n_compact + (units + per - 1) / per);
     const dim3 block(rm_units::kCompactThreads);
-    if (p.wdtype == RM_BF16)
-        hipLaunchKernelGGL(compact_prologue_kernel<true>, grid, block, 0, st, mask, p.d_ff, nseg, n_compact, idx,
-                           count, x, norm_g, p.d, nblk, units, xn, ssq);
-    else
-        hipLaunchKernelGGL(compact_prologue_kernel<false>, grid, block, 0, st, mask, p.d_ff, nseg, n_compact, idx,
-                           count, x, norm_g, p.d, nblk, units, xn, ssq);
+    hipLaunchKernelGGL(compact_prologue_kernel, grid, block, 0, st, mask, p.d_ff, nseg, n_compact, idx,
+                       count, x, norm_g, p.d, nblk, units, xn, ssq);
     return hipGetLastError();
 }
 
 hipError_t launch_prologue(const Plan &p, const float *x, const float *norm_g, void *ws, hipStream_t st) {
     char *base = static_cast<char *>(ws);
-    void *xn = base + p.off_xn;
+    uint16_t *xn = reinterpret_cast<uint16_t *>(base + p.off_xn);
     float *ssq = reinterpret_cast<float *>(base + p.off_ssq);
     const int nblk = (p.d + kRowBlock - 1) / kRowBlock;
     const dim3 grid(p.B * p.T * nblk);
-    if (p.wdtype == RM_BF16)
-        hipLaunchKernelGGL(prologue_kernel<true>, grid, dim3(kThreads), 0, st, x, norm_g, p.d, nblk, xn, ssq);
-    else
-        hipLaunchKernelGGL(prologue_kernel<false>, grid, dim3(kThreads), 0, st, x, norm_g, p.d, nblk, xn, ssq);
+    hipLaunchKernelGGL(prologue_kernel, grid, dim3(kThreads), 0, st, x, norm_g, p.d, nblk, xn, ssq);
     return hipGetLastError();
 }
 

@@ -212,9 +212,11 @@ rm_status run_layers(const rm::Plan &p, const rm_ffn_layer_weights *w, int L, co
                      const int32_t *idx, const int32_t *count, size_t list_stride, size_t count_stride, void *ws,
                      hipStream_t st, const AnchorTerms &at = AnchorTerms{}, const uint8_t *mask = nullptr,
                      int n_masks = 0) {
-    // The one-launch layer form reads the float32 input itself: only a mask's compaction precedes it.
+    // The one-launch layer form and the float32 kernels read the float32 input themselves: only a mask's
+    // compaction precedes them.
+    const bool bf = p.wdtype == RM_BF16;
     hipError_t e = hipSuccess;
-    if (p.xcd_layer) {
+    if (p.xcd_layer || !bf) {
         if (mask) e = rm::launch_mask_compact(mask, n_masks, p.d_ff, const_cast<int32_t *>(idx),
                                               const_cast<int32_t *>(count), st);
     } else {
@@ -223,7 +225,6 @@ rm_status run_layers(const rm::Plan &p, const rm_ffn_layer_weights *w, int L, co
                  : rm::launch_prologue(p, x, w[0].norm_g, ws, st);
     }
     if (e != hipSuccess) return hip_fail(e, "prologue launch");
-    const bool bf = p.wdtype == RM_BF16;
     const size_t y_stride = static_cast<size_t>(p.B) * p.T * p.d;
     // The fused down projection sums the whole list in each workgroup: fewer, longer workgroups than the split
     // over K, and no epilogue launch.  With one sample's 32-column tiles it is the faster form for every list
@@ -234,12 +235,12 @@ rm_status run_layers(const rm::Plan &p, const rm_ffn_layer_weights *w, int L, co
         const int32_t *cl = count + l * count_stride;
         const bool norm = w[l].norm_g != nullptr;
         const float *ha = at.ha_in ? at.ha_in + l * at.h_stride : nullptr;
+        const float *xin = l == 0 ? x : y;
         if (p.xcd_layer)  // gate/up and down in one launch from the float32 input; partials to the epilogue
-            e = rm::launch_layer_xcd(p, w[l].w_gate, w[l].w_up, w[l].w_down, il, cl, l == 0 ? x : y, w[l].norm_g,
-                                     ha, ws, st);
+            e = rm::launch_layer_xcd(p, w[l].w_gate, w[l].w_up, w[l].w_down, il, cl, xin, w[l].norm_g, ha, ws, st);
         else
             e = bf ? rm::launch_gateup_bf16(p, w[l].w_gate, w[l].w_up, il, cl, norm, ha, nullptr, ws, st)
-                   : rm::launch_gateup_f32(p, w[l].w_gate, w[l].w_up, il, cl, norm, ha, nullptr, ws, st);
+                   : rm::launch_gateup_f32(p, w[l].w_gate, w[l].w_up, il, cl, xin, w[l].norm_g, ha, nullptr, ws, st);
         if (e != hipSuccess) return hip_fail(e, p.xcd_layer ? "layer launch" : "gate/up launch");
         if (at.ha_out != nullptr) {  // the anchor keeps h^M of the group's lists (same input, same norm)
             const rm::Plan &q = *at.cap_plan;
@@ -247,23 +248,23 @@ rm_status run_layers(const rm::Plan &p, const rm_ffn_layer_weights *w, int L, co
             const int32_t *cc = at.cap_count + static_cast<size_t>(l) * p.B;
             float *ho = at.ha_out + l * at.h_stride;
             e = bf ? rm::launch_gateup_bf16(q, w[l].w_gate, w[l].w_up, ci, cc, norm, nullptr, ho, ws, st)
-                   : rm::launch_gateup_f32(q, w[l].w_gate, w[l].w_up, ci, cc, norm, nullptr, ho, ws, st);
+                   : rm::launch_gateup_f32(q, w[l].w_gate, w[l].w_up, ci, cc, xin, w[l].norm_g, nullptr, ho, ws, st);
             if (e != hipSuccess) return hip_fail(e, "anchor h capture launch");
         }
-        const bool next = l + 1 < L && !p.xcd_layer;  // the one-launch form needs no xn for the next layer
+        const bool next = l + 1 < L && !p.xcd_layer && bf;  // the others need no xn for the next layer
         const float *g_next = next ? w[l + 1].norm_g : nullptr;
-        const float *xin = l == 0 ? x : y;
         const float *ya_in = at.ya_in ? at.ya_in + l * y_stride : nullptr;
         float *ya_out = at.ya_out ? at.ya_out + l * y_stride : nullptr;
         if (fused) {  // down projection and epilogue in one launch
-            e = rm::launch_down_fused(p, w[l].w_down, il, cl, xin, y, g_next, next, ya_in, ya_out, w[l].out_gate,
-                                      ws, st);
+            e = bf ? rm::launch_down_fused(p, w[l].w_down, il, cl, xin, y, g_next, next, ya_in, ya_out,
+                                           w[l].out_gate, ws, st)
+                   : rm::launch_down_f32(p, w[l].w_down, il, cl, xin, y, ya_in, ya_out, w[l].out_gate, ws, st);
             if (e != hipSuccess) return hip_fail(e, "down launch");
             continue;
         }
         if (!p.xcd_layer) {
             e = bf ? rm::launch_down_bf16(p, w[l].w_down, il, ws, st)
-                   : rm::launch_down_f32(p, w[l].w_down, il, cl, ws, st);
+                   : rm::launch_down_f32(p, w[l].w_down, il, cl, xin, y, ya_in, ya_out, w[l].out_gate, ws, st);
             if (e != hipSuccess) return hip_fail(e, "down launch");
         }
         e = rm::launch_epilogue(p, cl, xin, y, g_next, next, ya_in, ya_out, w[l].out_gate, ws, st);
@@ -313,7 +314,7 @@ rm_status make_plan(const rm_ffn_shape *s, int B, int T, int max_count, Plan *p,
     const int kmax = max_count > 0 ? max_count : 1;
     size_t xn_elem, h_elem;
     bool xcd_shape = false, xcd_room = false;
-    int part_slices = 0;  // partial slices the workspace holds (at least q.slices)
+    int part_slices = 0;  // partial slices the workspace holds at least
     // Aim for one down-projection workgroup per compute unit (256 CUs): a grid just past a multiple of the unit
     // count leaves the units with one more workgroup setting the time (d = 2048, 4916 neurons: 8 slices of 20 chunks,
     // 256 workgroups, instead of 10 slices of 16, 320: down 10.0 -> 8.1 us), and fewer K-slices mean fewer
@@ -415,16 +416,43 @@ rm_status make_plan(const rm_ffn_shape *s, int B, int T, int max_count, Plan *p,
         xn_elem = 2;
         h_elem = 2;
     } else {
-        q.tpad = ceil_div(T, kF32TokBlock) * kF32TokBlock;
-        q.kcap = ceil_div(kmax, kF32NeurPerBlk) * kF32NeurPerBlk;
-        q.gate_blocks = q.kcap / kF32NeurPerBlk;
-        q.col_tile = kF32ColTile;
-        q.ncol = ceil_div(s->d, kF32ColTile);
-        const long long work = static_cast<long long>(kmax) * q.ncol * B;
-        const int su =
-            static_cast<int>(std::max<long long>(kF32SliceNeur, (work + kTargetDownGroups - 1) / kTargetDownGroups));
-        q.slice_units = su;
-        q.slices = ceil_div(kmax, su);
+        // The workspace keeps the room it always had (its size is part of the contract); the kernels' H, which
+        // starts at its beginning (they need no xn), and their partials lie within it.
+        const int room_ncol = ceil_div(s->d, kF32RoomCols);
+        const long long work = static_cast<long long>(kmax) * room_ncol * B;
+        const int room_neur =
+            static_cast<int>(std::max<long long>(kF32RoomSlice, (work + kTargetDownGroups - 1) / kTargetDownGroups));
+        const int room_slices = ceil_div(kmax, room_neur);
+        part_slices = room_slices;
+        q.kcap = ceil_div(kmax, kF32Chunk) * kF32Chunk;
+        q.tpad = T;
+        // Gate/up: the tokens in equal blocks of at most 32 (blocks of 64, one workgroup per compute unit: 4 samples
+        // of d = 1024 51.5 us per call, against 43.4), 8 neurons per workgroup, or 16, which read the input half as
+        // often and take 0.8 of the time per neuron where the rounds over the chip are equal (1229 neurons, T = 51:
+        // 308 workgroups 21.6, 154 20.2 us; 2500 neurons of d = 2048: 626 43.5, 313 46.9).
+        q.f32_tblocks = ceil_div(T, 32);
+        q.f32_nt = ceil_div(ceil_div(T, q.f32_tblocks), 16);
+        const long long groups = static_cast<long long>(ceil_div(kmax, 8)) * q.f32_tblocks * B;
+        auto rounds = [&](long long n) { return (n + kCUs - 1) / kCUs; };
+        q.gate_groups = 8 * rounds((groups + 1) / 2) <= 5 * rounds(groups) ? 2 : 1;
+        q.gate_blocks = ceil_div(ceil_div(kmax, 8 * q.gate_groups), 8) * 8;  // every sample's block i on the same XCD
+        // Down: 64 columns x 32 tokens per workgroup where that gives half the compute units one (2 samples of
+        // d = 1568, T = 120: 54.2 us in 32 x 16 tiles, 45.4), else 32 x 16.  The list is cut into slices (partials and
+        // the epilogue launch) only where fewer workgroups than half the compute units would share a list of over 64
+        // chunks: 3194 neurons at T = 1, 20 workgroups: 18.5 us in 4 slices, 20.5 in 2; 1229 neurons at T = 51, 128
+        // workgroups: 21.6 us in 2 slices, 21.2 in one.
+        const int nchunks = q.kcap / kF32Chunk;
+        const bool wide = static_cast<long long>(ceil_div(s->d, 64)) * ceil_div(T, 32) * B >= kCUs / 2;
+        q.df_nt = wide ? 2 : 1;
+        q.df_cw = wide ? 4 : 2;
+        q.ncol = ceil_div(s->d, 16 * q.df_cw);
+        const long long wgs = static_cast<long long>(q.ncol) * ceil_div(T, 16 * q.df_nt) * B;
+        const int want = static_cast<int>(std::min<long long>((kCUs / 2 + wgs - 1) / wgs, ceil_div(nchunks, 64)));
+        q.slices = std::max(1, std::min(want, room_slices));
+        const int slice_chunks = ceil_div(nchunks, q.slices);
+        q.slices = ceil_div(nchunks, slice_chunks);
+        q.slice_units = slice_chunks * kF32Chunk;
+        q.fused_down = q.slices == 1;
         xn_elem = 4;
         h_elem = 4;
     }
@@ -438,8 +466,10 @@ rm_status make_plan(const rm_ffn_shape *s, int B, int T, int max_count, Plan *p,
     size_t off = 0;
     q.off_xn = off;
     off = align_up(off + static_cast<size_t>(B) * T * s->d * xn_elem, 256);
-    q.off_h = off;
-    off = align_up(off + static_cast<size_t>(B) * q.tpad * q.kcap * h_elem, 256);
+    q.off_h = s->wdtype == RM_BF16 ? off : 0;
+    const int h_rows = s->wdtype == RM_BF16 ? q.tpad : ceil_div(T, kF32RoomTok) * kF32RoomTok;
+    const int h_cols = s->wdtype == RM_BF16 ? q.kcap : ceil_div(kmax, kF32RoomNeur) * kF32RoomNeur;
+    off = align_up(off + static_cast<size_t>(B) * h_rows * h_cols * h_elem, 256);
     q.off_part = off;
     off = align_up(off + static_cast<size_t>(B) * std::max(q.slices, part_slices) * static_cast<size_t>(T) * s->d * 4,
                    256);

@@ -54,11 +54,13 @@ constexpr int kSsqCols = 32;
 __host__ __device__ constexpr int ssq_parts(int d) { return (d + kSsqCols - 1) / kSsqCols; }
 __host__ __device__ constexpr int ssq_stride(int d) { return (ssq_parts(d) + 3) / 4 * 4; }
 
-// f32 path: vector ALU.
-constexpr int kF32TokBlock = 8;     // tokens per register block
-constexpr int kF32NeurPerBlk = 8;   // neurons per gate/up wave (8 lanes per neuron row)
-constexpr int kF32ColTile = 256;    // output columns per down wave (64 lanes x 4 columns)
-constexpr int kF32SliceNeur = 16;   // neurons per down K-slice
+// f32 path: 16x16x4 float32 matrix-core tiles.
+constexpr int kF32Chunk = 16;       // neurons per down-projection step (four calls of K = 4)
+// The float32 workspace's room (its size is part of the calls' contract): H and the partials lie within it.
+constexpr int kF32RoomTok = 8;      // H: tokens rounded up to
+constexpr int kF32RoomNeur = 8;     // H: neurons rounded up to
+constexpr int kF32RoomCols = 256;   // partials: columns per tile of the slice count
+constexpr int kF32RoomSlice = 16;   // partials: least neurons per slice of the slice count
 
 struct Plan {
     int d = 0, d_ff = 0, wdtype = 0, B = 0, T = 0, max_count = 0, act = RM_ACT_SILU;
@@ -83,12 +85,14 @@ struct Plan {
     int df_cw = 4;       // fused down: columns per lane (2 for one sample, 4 with several)
     int df_ncol = 0;     // fused down: column tiles of 16 df_cw columns
     int ntt = 0;         // fused down: token tiles of 16 df_nt tokens
+    int f32_nt = 4;      // f32 gate/up: 16-token tiles per token block
+    int f32_tblocks = 1; // f32 gate/up: token blocks
     // bf16, one sample, d = 2048, the spread plan's list lengths, 256 compute units: gate/up and down in one
     // launch (layer_xcd_kernel) that reads the float32 input itself, slices = the 8 XCDs' slices of slice_units
     // chunks; no prologue launch, the epilogue follows.
     bool xcd_layer = false;
-    // Workspace: xn [B][T][d] (bf16 or f32); H (bf16: [B][kcap / 32][tpad][32], chunk-major; f32:
-    // [B][tpad][kcap]); partials f32 [B][slices][T][d]; ssq f32 [B][T][ssq_stride(d)]
+    // Workspace: xn [B][T][d] (bf16; the f32 kernels read x itself); H, chunk-major (bf16: [B][kcap / 32][tpad][32];
+    // f32: [B][kcap / 16][T][16]); partials f32 [B][slices][T][d]; ssq f32 [B][T][ssq_stride(d)]
     // (per-token sums of squares of the FFN input by 32-column block, for the RMSNorm factor); and, for the dense
     // reference, the lists 0 .. d_ff-1 int32 [B][d_ff] and their counts int32 [B].
     // With xcd_layer, also the XCDs' own copies of the FFN input, bf16 [8][T][d], and of its partial sums of
@@ -159,7 +163,7 @@ hipError_t launch_group_masks(const float *h, int S, int L, int d_ff, int T, con
 // sparse kernels on them).
 hipError_t launch_identity_lists(const Plan &p, void *ws, hipStream_t st);
 
-// First layer's FFN input: xn = x * g (or x) in the FFN input dtype, and (norm only) its per-token sums of
+// The bf16 calls' first FFN input: xn = x * g (or x) in bf16, and (norm only) its per-token sums of
 // squares.
 hipError_t launch_prologue(const Plan &p, const float *x, const float *norm_g, void *ws, hipStream_t st);
 
@@ -174,9 +178,10 @@ hipError_t launch_compact_prologue(const Plan &p, const uint8_t *mask, int n_mas
 hipError_t launch_gateup_bf16(const Plan &p, const void *w_gate, const void *w_up, const int32_t *idx,
                               const int32_t *count, bool norm, const float *h_anchor, float *h_out, void *ws,
                               hipStream_t st);
+// The float32 form reads the layer's input x [B][T][d] itself and applies the norm (norm_g null: none).
 hipError_t launch_gateup_f32(const Plan &p, const void *w_gate, const void *w_up, const int32_t *idx,
-                             const int32_t *count, bool norm, const float *h_anchor, float *h_out, void *ws,
-                             hipStream_t st);
+                             const int32_t *count, const float *x, const float *norm_g, const float *h_anchor,
+                             float *h_out, void *ws, hipStream_t st);
 
 // Down projection of the listed neurons: per-K-slice float32 partials of H W_down[idx] in the workspace.  The
 // bf16 form needs no count: H is zero in every slot past the list.
@@ -192,7 +197,10 @@ hipError_t launch_down_fused(const Plan &p, const void *w_down, const int32_t *i
 hipError_t launch_layer_xcd(const Plan &p, const void *w_gate, const void *w_up, const void *w_down,
                             const int32_t *idx, const int32_t *count, const float *xin, const float *norm_g,
                             const float *h_anchor, void *ws, hipStream_t st);
-hipError_t launch_down_f32(const Plan &p, const void *w_down, const int32_t *idx, const int32_t *count, void *ws,
+// With p.fused_down the float32 form does the epilogue's work as well (launch_down_fused's arguments); else it leaves
+// partials for launch_epilogue.
+hipError_t launch_down_f32(const Plan &p, const void *w_down, const int32_t *idx, const int32_t *count,
+                           const float *x, float *y, const float *ya_in, float *ya_out, const float *out_gate, void *ws,
                            hipStream_t st);
 
 // y = x + the slices' partials in slice order; if emit_xn, also the next layer's FFN input (y * g_next, or y)

@@ -111,9 +111,8 @@ __device__ __forceinline__ void compact_segment(const uint8_t *__restrict__ mask
 }
 
 // Prologue of unit = row * nblk + blk (token row, block of 256 columns) by one wave; lane = the thread's lane.
-template <bool kBf16Out>
 __device__ __forceinline__ void prologue_unit(const float *__restrict__ x, const float *__restrict__ g, int d,
-                                              int nblk, void *__restrict__ xn, float *__restrict__ ssq, int unit,
+                                              int nblk, uint16_t *__restrict__ xn, float *__restrict__ ssq, int unit,
                                               int lane) {
     const int row = unit / nblk;
     const int blk = unit - row * nblk;
@@ -135,14 +134,10 @@ __device__ __forceinline__ void prologue_unit(const float *__restrict__ x, const
             v.z *= gv.z;
             v.w *= gv.w;
         }
-        if constexpr (kBf16Out) {
-            uint2 packed;
-            packed.x = rm_f32_to_bf16_bits(v.x) | (rm_f32_to_bf16_bits(v.y) << 16);
-            packed.y = rm_f32_to_bf16_bits(v.z) | (rm_f32_to_bf16_bits(v.w) << 16);
-            *reinterpret_cast<uint2 *>(static_cast<uint16_t *>(xn) + o) = packed;
-        } else {
-            *reinterpret_cast<float4 *>(static_cast<float *>(xn) + o) = v;
-        }
+        uint2 packed;
+        packed.x = rm_f32_to_bf16_bits(v.x) | (rm_f32_to_bf16_bits(v.y) << 16);
+        packed.y = rm_f32_to_bf16_bits(v.z) | (rm_f32_to_bf16_bits(v.w) << 16);
+        *reinterpret_cast<uint2 *>(xn + o) = packed;
     }
 }
 
