@@ -100,17 +100,16 @@ __global__ __launch_bounds__(kThreads) void select_rows_kernel(const float *__re
     __shared__ SelLds<kThreads> l;
     __shared__ uint8_t chosen[kThreads * kSelPerThread];
     const int tid = threadIdx.x;
-    const int p0 = tid * kSelPerThread;
     uint32_t valid = 0, key[kSelPerThread];
 #pragma unroll
     for (int i = 0; i < kSelPerThread; ++i) {
-        const bool ok = p0 + i < P;
-        if (ok) valid |= 1u << i;
-        key[i] = ok ? __float_as_uint(drift[p0 + i]) : 0u;  // drift >= 0: its bits order like its value
+        const int p = i * kThreads + tid;
+        if (p < P) valid |= 1u << i;
+        key[i] = P > 0 ? __float_as_uint(drift[min(p, P - 1)]) : 0u;  // drift >= 0: its bits order like its value
     }
     const uint32_t sel = select_top_k(key, valid, k, P, l);
 #pragma unroll
-    for (int i = 0; i < kSelPerThread; ++i) chosen[p0 + i] = static_cast<uint8_t>((sel >> i) & 1u);
+    for (int i = 0; i < kSelPerThread; ++i) chosen[i * kThreads + tid] = static_cast<uint8_t>((sel >> i) & 1u);
     __syncthreads();
     // Rows tid * 16 .. tid * 16 + 15 of the sequence, in order.
     const int r0 = tid * kSelPerThread;

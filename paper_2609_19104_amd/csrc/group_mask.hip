@@ -11,16 +11,13 @@
 // Kernels:
 //   neuron_norms_kernel:  one wave per 64 neurons; a 64 x 64 weight tile at a time goes through LDS (coalesced
 //                         row loads), then each lane adds its own row's 64 squares in column order.
-//   scores_kernel:        one wave per (step, layer, 64 neurons): the rows go through LDS with coalesced loads,
+//   scores_kernel:        one wave per (step, layer, 16 neurons): the rows go through LDS with coalesced loads,
 //                         then lane n adds row n in token order.
 //   step_select_kernel:   one workgroup per (step, layer), 16 neurons per thread (256 threads up to d_ff = 4096,
 //                         else 1024, d_ff <= 16384): the step's top K sets the layer's mask bytes (their union over
 //                         the steps).
 //   group_rerank_kernel:  one workgroup per layer (same size): the union's top K by summed score.
-// Top K is an MSB-first radix select over the scores' bit patterns (non-negative floats order like their bits):
-// four 8-bit passes, each a histogram (per-wave LDS histograms with integer atomics, so the counts are exact,
-// then added) and a suffix scan that finds the digit of the K-th largest key; then the keys above that
-// threshold plus the lowest-index keys equal to it, found with a workgroup prefix sum.
+// Top K: rm_select.h.
 #include "rm_select.h"
 
 namespace {
@@ -84,15 +81,16 @@ __global__ __launch_bounds__(64) void neuron_norms_kernel(const void *__restrict
 
 // ------------------------------------------------------------------------------------------ scores
 
-// One wave per (step and layer, 64 neurons).  The 64 rows of T floats are contiguous in h: the wave loads them
+// One wave per (step and layer, 16 neurons).  The 16 rows of T floats are contiguous in h: the wave loads them
 // (or 64-token slices of them) with consecutive lanes on consecutive addresses into LDS, then lane n adds |h| of
 // row n in token order.  The mask bytes of the layer are cleared here (step 0), before the selections set them.
-constexpr int kScoreRows = 64;
+// Bound by HBM: 75 MB at S = 5, L = 18, d_ff = 4096, T = 51, 14.5 us at the rate of a copy.  Small tiles, so that the
+// LDS lets a compute unit hold its 32 waves (64 rows: 9), and few loads per wave at a time: 64 rows with 32 loads
+// 18.9 us, 16 rows with 8 loads 15.9 (the whole rm_group_masks call with T = 50, d_ff = 4096: 47.8 and 33.1; two
+// steps of 12 layers of 15924 neurons, T = 74: 90.5 and 68.4).
+constexpr int kScoreRows = 16;
 constexpr int kScoreChunk = 64;
-#ifndef RM_SCORE_BATCH
-#define RM_SCORE_BATCH 32
-#endif
-constexpr int kScoreBatch = RM_SCORE_BATCH;  // loads in flight per lane
+constexpr int kScoreBatch = 8;  // loads in flight per lane
 
 // s + the n staged values added in index order, one rounding per addition (the chain continues across chunks),
 // with the LDS reads of 8 values issued before their additions.
@@ -103,16 +101,16 @@ __device__ __forceinline__ float row_abs_sum(float s, const float *row, int n) {
 #pragma unroll
         for (int i = 0; i < 8; ++i) q[i] = row[t + i];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) s = __fadd_rn(s, q[i]);
+        for (int i = 0; i < 8; ++i) s = __fadd_rn(s, fabsf(q[i]));
     }
-    for (; t < n; ++t) s = __fadd_rn(s, row[t]);
+    for (; t < n; ++t) s = __fadd_rn(s, fabsf(row[t]));
     return s;
 }
 
 __global__ __launch_bounds__(64) void scores_kernel(const float *__restrict__ h, int d_ff, int T,
                                                     const float *__restrict__ norms, int L,
                                                     float *__restrict__ scores, uint8_t *__restrict__ mask) {
-    __shared__ float tile[kScoreRows * (kScoreChunk + 1)];
+    __shared__ __attribute__((aligned(16))) float tile[kScoreRows * (kScoreChunk + 1)];
     const int lane = threadIdx.x;
     const int n0 = blockIdx.x * kScoreRows;
     const int sl = blockIdx.y;  // step * L + layer
@@ -131,7 +129,7 @@ __global__ __launch_bounds__(64) void scores_kernel(const float *__restrict__ h,
             for (int k = 0; k < kScoreBatch; ++k) v[k] = p[min(64 * (k0 + k), total - 1 - lane)];
 #pragma unroll
             for (int k = 0; k < kScoreBatch; ++k)
-                if (lane + 64 * (k0 + k) < total) tile[lane + 64 * (k0 + k)] = fabsf(v[k]);
+                if (lane + 64 * (k0 + k) < total) tile[lane + 64 * (k0 + k)] = v[k];
         }
         __syncthreads();
         if (lane < rows) s = row_abs_sum(s, tile + lane * T, T);
@@ -139,7 +137,7 @@ __global__ __launch_bounds__(64) void scores_kernel(const float *__restrict__ h,
         for (int t0 = 0; t0 < T; t0 += kScoreChunk) {
             const int C = min(kScoreChunk, T - t0);
             const int stride = C | 1;  // odd row pitch: lane n's reads of row n fall in distinct banks
-            const int total = rows * C;  // <= 64 x 64: at most 64 elements per lane
+            const int total = rows * C;  // <= 16 x 64: at most 16 elements per lane
             // The lane's elements e = lane + 64 k, (row r, token t) with e = r C + t stepped without a division,
             // in batches of kScoreBatch loads issued before any is used (elements past the chunk re-read its last
             // one and are not stored).
@@ -161,7 +159,7 @@ __global__ __launch_bounds__(64) void scores_kernel(const float *__restrict__ h,
                 }
 #pragma unroll
                 for (int k = 0; k < kScoreBatch; ++k) {
-                    if (lane + 64 * (k0 + k) < total) tile[rs * stride + ts] = fabsf(v[k]);
+                    if (lane + 64 * (k0 + k) < total) tile[rs * stride + ts] = v[k];
                     rs += dr;
                     ts += dt;
                     if (ts >= C) {
@@ -192,61 +190,70 @@ __global__ __launch_bounds__(kThreads) void step_select_kernel(const float *__re
                                                                int k, uint8_t *__restrict__ mask) {
     __shared__ SelLds<kThreads> l;
     const int sl = blockIdx.x;
-    const int n0 = threadIdx.x * kSelPerThread;
     const float *c = scores + static_cast<size_t>(sl) * d_ff;
     uint32_t valid = 0, key[kSelPerThread];
+    // Unconditional loads (items past d_ff read the last neuron and are not used).
 #pragma unroll
     for (int i = 0; i < kSelPerThread; ++i) {
-        const bool ok = n0 + i < d_ff;
-        if (ok) valid |= 1u << i;
-        key[i] = ok ? __float_as_uint(c[n0 + i]) : 0u;  // c >= 0: its bits order like its value
+        const int n = i * kThreads + static_cast<int>(threadIdx.x);
+        if (n < d_ff) valid |= 1u << i;
+        key[i] = __float_as_uint(c[min(n, d_ff - 1)]);  // c >= 0: its bits order like its value
     }
     const uint32_t sel = select_top_k(key, valid, k, d_ff, l);
     uint8_t *m = mask + static_cast<size_t>(sl % L) * d_ff;
 #pragma unroll
-    for (int i = 0; i < kSelPerThread; ++i)
-        if ((sel >> i) & 1u) m[n0 + i] = 1;  // several steps may set the same byte to the same value
+    for (int i = 0; i < kSelPerThread; ++i)  // several steps may set the same byte to the same value
+        if ((sel >> i) & 1u) m[i * kThreads + static_cast<int>(threadIdx.x)] = 1;
 }
 
 // The layer's mask: the K members of the union (mask bytes set by step_select_kernel) with the largest score
-// summed over the steps in step order.  Neurons outside the union get the smallest key and are never taken
-// (the union holds at least K neurons).
+// summed over the steps in step order.  The union holds at least K neurons.
+// Bound by latency: one workgroup per layer, whose loads are round trips.  18 layers of 4096 neurons, 5 steps: 18.6 us
+// with one step's scores in flight, each thread's 16 neurons consecutive (every load instruction touching 64 lines)
+// and digits from bit 31 on; 7.7 us with four steps in flight, the neurons dealt in turn, and rm_select.h's digits
+// (step_select_kernel, 90 workgroups: 9.0 -> 6.5 us).
 template <int kThreads>
 __global__ __launch_bounds__(kThreads) void group_rerank_kernel(const float *__restrict__ scores, int S, int L,
                                                                 int d_ff, int k, uint8_t *__restrict__ mask) {
     __shared__ SelLds<kThreads> l;
     const int layer = blockIdx.x;
-    const int n0 = threadIdx.x * kSelPerThread;
+    const int tid = threadIdx.x;
     uint8_t *m = mask + static_cast<size_t>(layer) * d_ff;
-    uint32_t valid = 0, key[kSelPerThread];
+    // No branch between the loads (a branch would let the compiler sink each load to its use, one round trip per
+    // neuron); items past d_ff read the last neuron and steps past S the last step, and are not used.
+    const int last = d_ff - 1;
+    constexpr int kSteps = kThreads == kSelThreadsSmall ? 4 : 2;  // (four spill at 1024 threads)
+    uint8_t in_union[kSelPerThread];
     float summed[kSelPerThread];
 #pragma unroll
     for (int i = 0; i < kSelPerThread; ++i) {
+        in_union[i] = m[min(i * kThreads + tid, last)];
         summed[i] = 0.0f;
-        if (n0 + i < d_ff) valid |= 1u << i;
     }
-    // The loads of a step are all issued before its sums, with no branch between them (a branch would let the
-    // compiler sink each load to its use, one round trip per neuron); slots past d_ff read the last neuron and
-    // are not used.
-    const int last = d_ff - 1;
-    for (int s = 0; s < S; ++s) {
-        const float *c = scores + (static_cast<size_t>(s) * L + layer) * d_ff;
-        float v[kSelPerThread];
+    for (int s0 = 0; s0 < S; s0 += kSteps) {
+        float v[kSteps][kSelPerThread];
 #pragma unroll
-        for (int i = 0; i < kSelPerThread; ++i) v[i] = c[min(n0 + i, last)];
+        for (int j = 0; j < kSteps; ++j) {
+            const float *c = scores + (static_cast<size_t>(min(s0 + j, S - 1)) * L + layer) * d_ff;
 #pragma unroll
-        for (int i = 0; i < kSelPerThread; ++i) summed[i] = __fadd_rn(summed[i], v[i]);
+            for (int i = 0; i < kSelPerThread; ++i) v[j][i] = c[min(i * kThreads + tid, last)];
+        }
+#pragma unroll
+        for (int j = 0; j < kSteps; ++j)
+#pragma unroll
+            for (int i = 0; i < kSelPerThread; ++i)
+                summed[i] = s0 + j < S ? __fadd_rn(summed[i], v[j][i]) : summed[i];
     }
-    uint8_t in_union[kSelPerThread];
+    uint32_t valid = 0, key[kSelPerThread];
 #pragma unroll
-    for (int i = 0; i < kSelPerThread; ++i) in_union[i] = m[min(n0 + i, last)];
-#pragma unroll
-    for (int i = 0; i < kSelPerThread; ++i)
-        key[i] = ((valid >> i) & 1u) && in_union[i] != 0 ? __float_as_uint(summed[i]) + 1u : 0u;
+    for (int i = 0; i < kSelPerThread; ++i) {
+        if (i * kThreads + tid < d_ff && in_union[i] != 0) valid |= 1u << i;
+        key[i] = __float_as_uint(summed[i]);
+    }
     const uint32_t sel = select_top_k(key, valid, k, d_ff, l);
 #pragma unroll
     for (int i = 0; i < kSelPerThread; ++i)
-        if ((valid >> i) & 1u) m[n0 + i] = static_cast<uint8_t>((sel >> i) & 1u);
+        if (i * kThreads + tid < d_ff) m[i * kThreads + tid] = static_cast<uint8_t>((sel >> i) & 1u);
 }
 
 }  // namespace

@@ -1,10 +1,12 @@
 // Device helpers shared by the kernels that rank float32 scores: an exactly rounded product, a workgroup prefix
 // sum, and the top-K selection of a workgroup of 256 or 1024 threads (group_mask.hip, context_cache.hip).
 //
-// Top K is an MSB-first radix select over the scores' bit patterns (non-negative floats order like their bits):
-// four 8-bit passes, each a histogram (per-wave LDS histograms with integer atomics, so the counts are exact,
-// then added) and a suffix scan that finds the digit of the K-th largest key; then the keys above that
-// threshold plus the lowest-index keys equal to it, found with a workgroup prefix sum.
+// Top K is an MSB-first radix select over the scores' bit patterns (non-negative floats order like their bits), taken
+// relative to the smallest key and from the highest bit in which the keys differ: passes of 8 bits, each a histogram
+// (per-wave LDS histograms with integer atomics, so the counts are exact, then added) and a suffix scan that finds the
+// digit of the K-th largest key, until every key of that digit is taken (mostly after two passes) or the bits end;
+// then, of keys equal to the K-th largest, the lowest-index ones, by ballots and a prefix sum of their counts.  Digits
+// from bit 31 on would put nearly all keys of one magnitude into a few counters, whose atomics then run one by one.
 #pragma once
 
 #include "rm_internal.h"
@@ -25,11 +27,14 @@ __device__ __forceinline__ float mul_rounded(float a, float b) {
 
 template <int kThreads>
 struct SelLds {
+    static constexpr int kWaves = kThreads / 64;
     // One histogram per wave (atomics only contend within a wave), two sets: a pass counts into one while the
     // other is cleared for the next pass.
-    uint32_t whist[2][kThreads / 64][256];
-    int wave_sum[kThreads / 64];
-    int digit, need;
+    uint32_t whist[2][kWaves][256];
+    uint32_t wave_lo[kWaves], wave_hi[kWaves];
+    int wave_sum[kWaves];
+    int eq_before[kSelPerThread * kWaves];  // items equal to the K-th largest before each run of 64 items
+    int digit, need, in_digit;
 };
 
 // Inclusive prefix sum over the 64 lanes of a wave (every lane active), with DPP moves instead of LDS
@@ -58,8 +63,10 @@ __device__ __forceinline__ int block_excl_scan(int v, SelLds<kThreads> &l) {
     return before + incl - v;
 }
 
-// Selection bits (bit i: item tid * 16 + i) of the k largest keys among the thread's valid ones (bit i of
-// `valid`), ties to the lower item index.  0 <= k; every thread of the workgroup calls it.
+// Items are dealt to the threads in turn: item i * kThreads + tid is the thread's i-th, so that a wave's loads and
+// stores of one i are consecutive.  Selection bits (bit i: the thread's i-th item) of the k largest keys among the
+// valid ones (bit i of `valid`; n_valid of them in the workgroup or more), ties to the lower item index.  0 <= k; every
+// thread of the workgroup calls it.
 template <int kThreads>
 __device__ inline uint32_t select_top_k(const uint32_t (&key)[kSelPerThread], uint32_t valid, int k, int n_valid,
                                         SelLds<kThreads> &l) {
@@ -68,18 +75,44 @@ __device__ inline uint32_t select_top_k(const uint32_t (&key)[kSelPerThread], ui
     if (k >= n_valid) return valid;
     constexpr int kWaves = kThreads / 64;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    uint32_t prefix = 0, hi = 0;
-    int need = k;
+    uint32_t lo = 0xffffffffu, hi = 0u;
+#pragma unroll
+    for (int i = 0; i < kSelPerThread; ++i)
+        if ((valid >> i) & 1u) {
+            lo = min(lo, key[i]);
+            hi = max(hi, key[i]);
+        }
+    for (int off = 1; off < 64; off <<= 1) {
+        lo = min(lo, static_cast<uint32_t>(__shfl_xor(static_cast<int>(lo), off)));
+        hi = max(hi, static_cast<uint32_t>(__shfl_xor(static_cast<int>(hi), off)));
+    }
+    if (lane == 0) {
+        l.wave_lo[wave] = lo;
+        l.wave_hi[wave] = hi;
+    }
     for (int b = lane; b < 256; b += 64) l.whist[0][wave][b] = 0u;
     __syncthreads();
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+        lo = min(lo, l.wave_lo[w]);
+        hi = max(hi, l.wave_hi[w]);
+    }
+    // Keys relative to lo, `bits` bits wide.  A pass splits the keys whose bits above `shift + width` equal prefix.
+    const int bits = hi > lo ? 32 - __clz(hi - lo) : 1;
+    int shift = bits, need = k;
+    uint32_t prefix = 0;
+    bool all = false;  // every key with the prefix is taken
     // Two barriers per pass: after the counts, and after wave 0 has found the digit (meanwhile the other waves
     // clear the other histogram set for the next pass).
-    for (int pass = 0; pass < 4; ++pass) {
-        const int shift = 24 - 8 * pass, buf = pass & 1;
+    for (int pass = 0; shift > 0 && !all; ++pass) {
+        const int width = min(8, shift), buf = pass & 1;
+        shift -= width;
 #pragma unroll
-        for (int i = 0; i < kSelPerThread; ++i)
-            if (((valid >> i) & 1u) && (key[i] & hi) == prefix)
-                atomicAdd(&l.whist[buf][wave][(key[i] >> shift) & 255u], 1u);
+        for (int i = 0; i < kSelPerThread; ++i) {
+            const uint32_t q = (key[i] - lo) >> shift;
+            if (((valid >> i) & 1u) && (q >> width) == prefix)
+                atomicAdd(&l.whist[buf][wave][q & ((1u << width) - 1u)], 1u);
+        }
         __syncthreads();
         if (wave == 0) {  // lane j holds digits 4j .. 4j+3; find the digit holding the need-th largest key
             uint32_t b[4] = {0u, 0u, 0u, 0u};
@@ -97,6 +130,7 @@ __device__ inline uint32_t select_top_k(const uint32_t (&key)[kSelPerThread], ui
                 if (cum < need && cum + c >= need) {
                     l.digit = 4 * lane + q;
                     l.need = need - cum;
+                    l.in_digit = c;
                 }
                 cum += c;
             }
@@ -104,26 +138,48 @@ __device__ inline uint32_t select_top_k(const uint32_t (&key)[kSelPerThread], ui
             for (int w = wave - 1; w < kWaves; w += kWaves - 1)
                 for (int b = lane; b < 256; b += 64) l.whist[buf ^ 1][w][b] = 0u;
         }
-        __syncthreads();  // l.digit / l.need are rewritten by wave 0 only after the next pass's first barrier
-        prefix |= static_cast<uint32_t>(l.digit) << shift;
-        hi |= 255u << shift;
+        __syncthreads();  // l.digit and the rest are rewritten by wave 0 only after the next pass's first barrier
+        prefix = (prefix << width) | static_cast<uint32_t>(l.digit);
         need = l.need;
+        all = l.in_digit == need;
     }
-    // prefix is the k-th largest key; take every larger key and the `need` lowest-index keys equal to it.
+    // Take every key above the prefix, and those with it: all, or the `need` lowest-index ones.
     uint32_t sel = 0, eq = 0;
 #pragma unroll
     for (int i = 0; i < kSelPerThread; ++i) {
         if (!((valid >> i) & 1u)) continue;
-        if (key[i] > prefix) sel |= 1u << i;
-        if (key[i] == prefix) eq |= 1u << i;
+        const uint32_t q = (key[i] - lo) >> shift;
+        if (q > prefix) sel |= 1u << i;
+        if (q == prefix) eq |= 1u << i;
     }
-    int rank = block_excl_scan(__popc(eq), l);
+    if (all) return sel | eq;
 #pragma unroll
     for (int i = 0; i < kSelPerThread; ++i) {
-        if ((eq >> i) & 1u) {
-            if (rank < need) sel |= 1u << i;
-            ++rank;
+        const unsigned long long b = __ballot((eq >> i) & 1u);
+        if (lane == 0) l.eq_before[i * kWaves + wave] = __popcll(b);
+    }
+    __syncthreads();
+    if (wave == 0) {  // their exclusive prefix sum, in item order
+        constexpr int kEach = kSelPerThread * kWaves / 64;
+        int c[kEach], own = 0;
+#pragma unroll
+        for (int j = 0; j < kEach; ++j) {
+            c[j] = l.eq_before[lane * kEach + j];
+            own += c[j];
         }
+        int before = wave_incl_scan(own) - own;
+#pragma unroll
+        for (int j = 0; j < kEach; ++j) {
+            l.eq_before[lane * kEach + j] = before;
+            before += c[j];
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kSelPerThread; ++i) {
+        const unsigned long long b = __ballot((eq >> i) & 1u);
+        const int rank = l.eq_before[i * kWaves + wave] + __popcll(b & ((1ull << lane) - 1ull));
+        if (((eq >> i) & 1u) && rank < need) sel |= 1u << i;
     }
     return sel;
 }
