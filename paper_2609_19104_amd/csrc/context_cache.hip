@@ -25,10 +25,17 @@
 // allows: 256 rows by 128 columns of each weight matrix (2 MB read per gate/up workgroup over K = 2048), 8 waves
 // each accumulating 64 x 64 per matrix, K staged 64 wide (one cache line per row) straight from memory into LDS.
 // Workgroups that share a weight tile are numbered onto one XCD so that its L2 serves the re-reads.
+#include "rm_dma.h"
 #include "rm_select.h"
 
 namespace {
 
+using rm_dma::dma16;
+using rm_dma::kRowBytes;
+using rm_dma::kStageK;
+using rm_dma::lds_addr;
+using rm_dma::row_swz;
+using rm_dma::wait_barrier;
 using rm_sel::kSelPerThread;
 using rm_sel::kSelThreads;
 using rm_sel::kSelThreadsSmall;
@@ -131,20 +138,14 @@ __global__ __launch_bounds__(kThreads) void select_rows_kernel(const float *__re
 
 // The GEMM operands live in a blocked layout: a bf16 matrix [R][K] (R and K multiples of 64) as 64-row x 64-column
 // blocks of 8 KB, the blocks of one 64-row tile consecutive along K.  Inside a block, row r holds its 64 columns
-// (128 bytes) as eight 16-byte pieces, piece p at position p ^ swz(r): a block is the exact image of its rows in
-// the GEMM's LDS stage, so one K stage of a tile is one contiguous read.  swz permutes the pieces so that the
-// matrix-core fragment reads (16 rows at one piece) hit distinct LDS banks, both with 32 banks served 8 lanes a
-// cycle and with 64 banks served 16 lanes a cycle (the counters show no conflicts).
-constexpr int kStageK = 64;                       // K per GEMM stage and per block column
-constexpr int kRowBytes = kStageK * 2;
+// (128 bytes) as eight 16-byte pieces, piece p at position p ^ row_swz(r): a block is the exact image of its rows in
+// the GEMM's LDS stage (rm_dma.h), so one K stage of a tile is one contiguous read.
 constexpr int kBlockElems = 64 * kStageK;
-
-__device__ __forceinline__ int ctx_swz(int r) { return (r ^ (r >> 3)) & 7; }  // r: row mod 16
 
 __device__ __forceinline__ size_t blocked_offset(int row, int col, int K) {  // element offset of (row, col)
     const int r = row & 63, piece = (col % kStageK) >> 3;
     return (static_cast<size_t>(row >> 6) * (K / kStageK) + col / kStageK) * kBlockElems + r * kStageK +
-           ((piece ^ ctx_swz(r & 15)) << 3) + (col & 7);
+           ((piece ^ row_swz(r & 15)) << 3) + (col & 7);
 }
 
 // Weight packing: one thread per 16-byte piece of a row-major [R][K] matrix.
@@ -213,30 +214,6 @@ struct GemmArgs {
 // so each load reads 1 KB of consecutive memory; a row-major B is read 128 bytes per row, each lane taking the
 // piece that belongs at its position.
 
-// One load of 16 bytes per lane into LDS at lds + 16 lane (M0 holds the wave's LDS base while it issues; M0 is
-// the compiler's register, so its value is kept and put back).  Issued as inline assembly so that the compiler,
-// which cannot tell the stage buffers apart, adds no wait of its own for it before the LDS reads: the waits are
-// the explicit ones below.
-__device__ __forceinline__ void dma16(const void *g, uint32_t lds) {
-    uint32_t keep;
-    asm volatile(
-        "s_mov_b32 %0, m0\n\ts_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off\n\ts_mov_b32 m0, %0"
-        : "=&s"(keep)
-        : "v"(g), "s"(lds)
-        : "memory");
-}
-
-// Wait until at most N of this wave's vector-memory operations are in flight and all its LDS operations are
-// done, then the workgroup barrier.  The compiler may not move memory accesses across it.
-template <int N>
-__device__ __forceinline__ void dma_wait_barrier() {
-    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
-}
-
-__device__ __forceinline__ uint32_t lds_addr(const uint8_t *p) {
-    return static_cast<uint32_t>(reinterpret_cast<uintptr_t>((const __attribute__((address_space(3))) uint8_t *)p));
-}
-
 // Waves per SIMD that the stage buffers allow (160 KB of LDS per compute unit), at most 2: the register budget
 // follows from it.
 constexpr int dma_waves_per_simd(int lds_bytes, int waves) {
@@ -301,7 +278,7 @@ void gemm_dma_kernel(GemmArgs a) {
         } else {
             constexpr int kPieces = kStageK / 8;
             const int rr = mrow + lane / kPieces;  // row of this lane's piece
-            const int piece = (lane % kPieces) ^ ctx_swz(rr & 15);
+            const int piece = (lane % kPieces) ^ row_swz(rr & 15);
             src[j] = base + static_cast<size_t>(rr) * a.K + k_base + piece * 8;
         }
     }
@@ -328,7 +305,7 @@ void gemm_dma_kernel(GemmArgs a) {
     auto compute = [&](const uint8_t *buf) {
 #pragma unroll
         for (int ks = 0; ks < kStageK / 32; ++ks) {
-            const int frag = r * kRowBytes + (((ks * 4 + grp) ^ ctx_swz(r)) << 4);
+            const int frag = r * kRowBytes + (((ks * 4 + grp) ^ row_swz(r)) << 4);
             rm_u32x4 af[TM], bf[NB][TN];
 #pragma unroll
             for (int tm = 0; tm < TM; ++tm)
@@ -357,11 +334,11 @@ void gemm_dma_kernel(GemmArgs a) {
     for (int kt = 0; kt < nk; ++kt) {
         const int later = min(nk - 1 - kt, STAGES - 2);  // stages issued after kt
         if (STAGES >= 4 && later >= 2)
-            dma_wait_barrier<(STAGES >= 4 ? 2 : 0) * BPW>();
+            wait_barrier<(STAGES >= 4 ? 2 : 0) * BPW>();
         else if (STAGES >= 3 && later == 1)
-            dma_wait_barrier<BPW>();
+            wait_barrier<BPW>();
         else
-            dma_wait_barrier<0>();
+            wait_barrier<0>();
         if (kt + STAGES - 1 < nk) issue(kt + STAGES - 1);
         compute(&lds[kt % STAGES][0]);
     }

@@ -20,6 +20,7 @@
 //   gateup_staged:  NG groups (16..64 neurons) per workgroup, 8 / NG waves per group splitting d; B is
 //                   staged in LDS in 256-column chunks (double-buffered) and shared by all NG groups, so each
 //                   byte of xn read from L2 serves NG times more neurons.
+//   gateup_tile:    many groups over samples and token blocks, see there.
 //   Both sum the d-split waves in LDS in a fixed order, then write h = SiLU(r g) * (r u) to H[t][slot] in
 //   bf16.  Slots past the list get h = 0 so that the down projection can read whole 32-neuron chunks.
 //
@@ -33,6 +34,7 @@
 //   down_fused: for lists of at most 64 chunks, one workgroup sums the whole list for its tile and does the
 //   epilogue's work: one sample, 32 columns (2 per lane, 2 calls per chunk) and 16 tokens; several samples, 64
 //   columns and the whole 64-token block, the chunks in stages.
+#include "rm_dma.h"
 #include "rm_internal.h"
 
 namespace {
@@ -615,6 +617,199 @@ __global__ __launch_bounds__(kGuThreads, (NG == 2 || kTwoPerCU) ? 4 : 2) void ga
     for (int gg = 0; gg < NG; ++gg)
         gu_store_h<NT>(a, Hb, b, [&](int w2, int tt, int l) -> const rm_f32x4 & { return red(gg, w2, tt, l); }, DS, 0,
                        blk0 + gg * 8 + (tid & 7), cnt, rt);
+}
+
+// ------------------------------------------------------------------------------------------ gate / up, tiled
+
+// For calls with many groups of 8 listed neurons over all samples and token blocks (the plan's rule): up to 4 TPW groups
+// (16-row weight tiles) x one block of 16 NT tokens of one sample per workgroup, any d.  Both operands go straight from
+// memory into LDS in 64-column stages (whole 128-byte lines, 8 rows per load), kTileStages buffers, all but one in
+// flight.  Wave w takes K step w / 4 (32 columns) of every stage for tiles w % 4, w % 4 + 4, ..., so a stage's input
+// serves all tiles from LDS, and the two K halves are added through LDS.
+// What bounds it: 16 samples of 51 tokens, 1229 of 4096 neurons, d = 1024 (10 groups per workgroup, 256 workgroups, one
+// round) take 16.3 us, of which 9.8 are the launch, the indices', the first stages' round trips and the reduction, 5 the
+// products and their barriers and under 2 waiting for later stages (timed without loads and without the loop).  The
+// pipelined kernel took 21.5: its weights go from memory to registers in fragment order, which the L1 looks up row by
+// row (6.6 M lookups, half of its time; 2.3 M here), and 624 workgroups ran in two rounds.
+// Tried, slower: the next stage's fragments read ahead of the products (+0.5 us), h formed in registers after a
+// v_permlane32_swap (+0.9 us).
+constexpr int kTileStages = 4;
+constexpr int tile_rows(int NT, int TPW) { return 64 * TPW + 16 * NT; }
+
+template <int NT, int TPW>
+__global__ __launch_bounds__(kGuThreads, 2) void gateup_tile_kernel(GuArgs a, int tiles, int tblocks) {
+    constexpr int kMaxTiles = 4 * TPW;
+    constexpr int kUnits = 2 * NT + 2 * kMaxTiles;                 // loads of 8 rows per stage: input, then weights
+    constexpr int U = (kUnits + kGuWaves - 1) / kGuWaves;          // of them per wave
+    constexpr int STAGE = U * kGuWaves * 8 * rm_dma::kRowBytes;    // bytes (rows past the last unit: never read)
+    constexpr int S = kTileStages;
+    static_assert(kGuWaves == 8 && S >= 3 && U * (S - 2) <= 63, "two K steps x four tile columns; vmcnt range");
+    static_assert(2 * kMaxTiles * NT * 1024 <= S * STAGE, "the two K halves' tiles fit the stages");
+    __shared__ __attribute__((aligned(1024))) uint8_t lds[S * STAGE];
+    __shared__ float spans[64 * 9];
+
+    const int q = xcd_logical(blockIdx.x, gridDim.x);  // = (block * tblocks + token block) * B + sample
+    const int b = q % a.B;
+    const int t0 = (q / a.B) % tblocks * 16 * NT;
+    const int slot0 = (q / a.B) / tblocks * tiles * 8;
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r = lane & 15;
+    const int grp = lane >> 4;
+    const int raw_cnt = a.count[b];
+    uint16_t *Hb = a.H + static_cast<size_t>(b) * a.tpad * a.kcap;
+
+    // Source of the lane's 16 bytes in each of the wave's units (unit wave + 8 u) at stage 0: row lane / 8 of 8, the
+    // piece that belongs at its position.  Units past the workgroup's tiles read one address.
+    const int row8 = lane >> 3, pos = lane & 7;
+    int raw_n[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int w = wave + 8 * u - 2 * NT;  // weight unit: tile w / 2, gate rows (even) or up rows (odd)
+        raw_n[u] = a.idx[static_cast<size_t>(b) * a.d_ff + min(slot0 + max(w >> 1, 0) * 8 + row8, a.d_ff - 1)];
+    }
+    // The token block's partial sums of squares, span tid % 8 of token tid / 8 (d <= 2048; wider rows: below).
+    const int nparts = rm::ssq_parts(a.d), stride = rm::ssq_stride(a.d);
+    const bool few_spans = nparts <= 64;
+    float4 sp_lo = make_float4(0.f, 0.f, 0.f, 0.f), sp_hi = sp_lo;
+    if (a.ssq != nullptr && few_spans) {
+        const float *row = a.ssq + static_cast<size_t>(b * a.T + min(t0 + (tid >> 3), a.T - 1)) * stride;
+        sp_lo = *reinterpret_cast<const float4 *>(row + min(8 * (tid & 7), stride - 4));
+        sp_hi = *reinterpret_cast<const float4 *>(row + min(8 * (tid & 7) + 4, stride - 4));
+    }
+    const int cnt = clamp_count(raw_cnt, a.max_count);
+    if (slot0 >= cnt) {  // nothing listed: h = 0 (nothing to capture for an anchor)
+        if (a.h_out != nullptr) return;
+        for (int e = tid; e < 16 * NT * tiles; e += kGuThreads) {
+            const int t = t0 + e / tiles, slot = slot0 + (e % tiles) * 8;
+            if (slot < a.kcap)
+                *reinterpret_cast<rm_u32x4 *>(Hb + (static_cast<size_t>(slot >> 5) * a.tpad + t) * rm::kBfChunk +
+                                              (slot & 31)) = zero16();
+        }
+        return;
+    }
+    const uint16_t *src[U];
+    bool whole[U];  // the unit's pieces 4 .. 7 exist in a last stage of 32 columns too (a fixed address)
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int unit = wave + 8 * u, w = unit - 2 * NT;
+        whole[u] = false;
+        if (w < 0) {
+            const int t = t0 + unit * 8 + row8;
+            src[u] = a.xn + static_cast<size_t>(b * a.T + min(t, a.T - 1)) * a.d +
+                     ((pos ^ rm_dma::row_swz((unit * 8 + row8) & 15)) << 3);
+        } else if ((w >> 1) < tiles) {
+            src[u] = ((w & 1) ? a.wu : a.wg) + static_cast<size_t>(clamp_neuron(raw_n[u], a.d_ff)) * a.d +
+                     ((pos ^ rm_dma::row_swz((w & 1) * 8 + row8)) << 3);
+        } else {
+            src[u] = a.xn;
+            whole[u] = true;
+        }
+    }
+    const uint32_t lds0 = rm_dma::lds_addr(lds);
+    // Step k processes stage (k + rot) mod nk: rows are often 2 or 4 KB apart, and workgroups that all read the same 128
+    // bytes of their rows would load a few L2 and memory channels only.
+    const int nk = (a.d + 63) / 64;
+    const int rot = a.B == 1 ? q % nk : 0;
+    auto stage_of = [&](int k) { return k + rot < nk ? k + rot : k + rot - nk; };
+    auto issue = [&](int k) {
+        const int kt = stage_of(k);
+        const uint32_t buf = lds0 + (k % S) * STAGE;
+        // In a last stage of 32 columns the pieces past the row re-read the row's last 32 columns; they are not used.
+        const bool half = kt == nk - 1 && (a.d & 32) != 0;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const uint16_t *p = src[u] + (whole[u] ? 0 : kt * 64);
+            if (half && !whole[u]) {
+                const int unit = wave + 8 * u, w = unit - 2 * NT;
+                const int rr = w < 0 ? (unit * 8 + row8) & 15 : (w & 1) * 8 + row8;
+                if ((pos ^ rm_dma::row_swz(rr)) >= 4) p -= 32;
+            }
+            rm_dma::dma16(p, __builtin_amdgcn_readfirstlane(buf + (wave + 8 * u) * 1024));
+        }
+    };
+    rm_f32x4 acc[TPW][NT];
+#pragma unroll
+    for (int j = 0; j < TPW; ++j)
+#pragma unroll
+        for (int tt = 0; tt < NT; ++tt) acc[j][tt] = rm_f32x4{0.f, 0.f, 0.f, 0.f};
+    const int ks = wave >> 2, col = wave & 3;
+    const int frag = r * rm_dma::kRowBytes + (((ks * 4 + grp) ^ rm_dma::row_swz(r)) << 4);
+    auto fence = [&](int stages) {  // at most the last `stages` issued stages' loads in flight, then the barrier
+        if (stages >= 2)
+            rm_dma::wait_barrier<2 * U>();
+        else if (stages == 1)
+            rm_dma::wait_barrier<U>();
+        else
+            rm_dma::wait_barrier<0>();
+    };
+    static_assert(S == 4, "the waits above");
+#pragma unroll
+    for (int s = 0; s < S - 1; ++s)
+        if (s < nk) issue(s);
+    for (int k = 0; k < nk; ++k) {
+        // Stage k has arrived (later ones stay in flight); past the barrier every wave is also done with the buffer read
+        // at step k - 1, which stage k + S - 1 refills.
+        fence(min(nk - 1 - k, S - 2));
+        if (k + S - 1 < nk) issue(k + S - 1);
+        if (ks * 32 + stage_of(k) * 64 >= a.d) continue;  // the second half of a 32-column last stage
+        const uint8_t *buf = lds + (k % S) * STAGE + frag;
+        rm_u32x4 bx[NT];
+#pragma unroll
+        for (int tt = 0; tt < NT; ++tt) bx[tt] = *reinterpret_cast<const rm_u32x4 *>(buf + tt * 16 * rm_dma::kRowBytes);
+#pragma unroll
+        for (int j = 0; j < TPW; ++j) {
+            if (col + 4 * j >= tiles) break;
+            const rm_u32x4 w =
+                *reinterpret_cast<const rm_u32x4 *>(buf + (16 * NT + (col + 4 * j) * 16) * rm_dma::kRowBytes);
+#pragma unroll
+            for (int tt = 0; tt < NT; ++tt) acc[j][tt] = mfma_bf16(w, bx[tt], acc[j][tt]);
+        }
+    }
+    __syncthreads();  // every wave is done with the stages before they hold the tiles
+    // Lane l's slot in a tile: rows 4-7 and 12-15 (odd 16-lane groups) start half a bank row further, so that gu_store_h's
+    // reads of 8 rows x 8 tokens touch every bank once.
+    auto red = [&](int k, int tile, int tt, int l) -> rm_f32x4 & {
+        return reinterpret_cast<rm_f32x4 *>(lds)[((k * kMaxTiles + tile) * NT + tt) * 64 + (l ^ ((l >> 1) & 8))];
+    };
+#pragma unroll
+    for (int j = 0; j < TPW; ++j)
+#pragma unroll
+        for (int tt = 0; tt < NT; ++tt) red(ks, col + 4 * j, tt, lane) = acc[j][tt];
+    if (a.ssq != nullptr && few_spans) {  // partials past the row add +0 (the sums are not negative: no change)
+        const int k = 8 * (tid & 7);
+        const float4 lo = make_float4(k < nparts ? sp_lo.x : 0.f, k + 1 < nparts ? sp_lo.y : 0.f,
+                                      k + 2 < nparts ? sp_lo.z : 0.f, k + 3 < nparts ? sp_lo.w : 0.f);
+        const float4 hi = make_float4(k + 4 < nparts ? sp_hi.x : 0.f, k + 5 < nparts ? sp_hi.y : 0.f,
+                                      k + 6 < nparts ? sp_hi.z : 0.f, k + 7 < nparts ? sp_hi.w : 0.f);
+        spans[(tid >> 3) * 9 + (tid & 7)] = rm_ssq_span(lo, hi);
+    }
+    // This thread's neuron of every tile and token; Eq. 4's anchor values of all tiles go out before their use.
+    const int j8 = tid & 7, tok = tid >> 3;
+    float ha[kMaxTiles];
+    if (a.h_anchor != nullptr)
+#pragma unroll
+        for (int i = 0; i < kMaxTiles; ++i) ha[i] = anchor_h(a, b, slot0 + i * 8 + j8, t0 + tok);
+    __syncthreads();
+    if (tok >= 16 * NT) return;
+    float rt = 1.0f;
+    if (a.ssq != nullptr && t0 + tok < a.T) {
+        if (few_spans) {
+            float s = spans[tok * 9];
+            for (int k = 1; k * 8 < nparts; ++k) s += spans[tok * 9 + k];
+            rt = rm_rnorm_from_ssq(s, a.d, a.eps);
+        } else {
+            rt = rm_token_rnorm(a.ssq, b * a.T + t0 + tok, a.d, a.eps);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < kMaxTiles; ++i) {
+        if (i >= tiles) continue;
+        const int slot = slot0 + i * 8 + j8;
+        gu_store_h<NT>(a, Hb, b, [&](int k, int tt, int l) -> const rm_f32x4 & { return red(k, i, tt, l); }, 2, t0,
+                       slot < a.kcap ? slot : -1, cnt, rt, true, ha[i]);
+    }
 }
 
 // ------------------------------------------------------------------------------------------ gate / up, spread
@@ -1679,6 +1874,26 @@ static hipError_t launch_gateup_args(const Plan &p, const GuArgs &a, hipStream_t
         else
             RM_SPREAD(3)
 #undef RM_SPREAD
+        return e != hipSuccess ? e : hipGetLastError();
+    }
+    if (p.gate_tiles > 0) {
+        const dim3 grid(p.gate_blocks * p.gate_tblocks * p.B), block(kGuThreads);
+#define RM_TILE(NT)                                                                                          \
+    switch ((p.gate_tiles + 3) / 4) {                                                                        \
+        case 1: e = launch_timed(RM_KERNEL_GATEUP, gateup_tile_kernel<NT, 1>, grid, block, st, a, p.gate_tiles, \
+                                 p.gate_tblocks); break;                                                     \
+        case 2: e = launch_timed(RM_KERNEL_GATEUP, gateup_tile_kernel<NT, 2>, grid, block, st, a, p.gate_tiles, \
+                                 p.gate_tblocks); break;                                                     \
+        default: e = launch_timed(RM_KERNEL_GATEUP, gateup_tile_kernel<NT, 3>, grid, block, st, a, p.gate_tiles, \
+                                  p.gate_tblocks); break;                                                    \
+    }
+        switch (p.gate_nt) {
+            case 1: RM_TILE(1) break;
+            case 2: RM_TILE(2) break;
+            case 3: RM_TILE(3) break;
+            default: RM_TILE(4) break;
+        }
+#undef RM_TILE
         return e != hipSuccess ? e : hipGetLastError();
     }
     switch (token_tiles(p.T)) {

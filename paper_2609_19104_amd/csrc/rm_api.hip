@@ -361,6 +361,30 @@ rm_status make_plan(const rm_ffn_shape *s, int B, int T, int max_count, Plan *p,
             q.gate_spread = (ceil_div(k32 / 4, kCUs) + 1) / 2;  // 16-row tiles of the fullest workgroup
             q.gate_blocks = kCUs;
         }
+        // Four groups of 8 slots per compute unit or more, over all samples and token blocks: the tiled kernel, whose
+        // workgroups share a staged input between up to 12 groups.  Below that its longer workgroups leave too little
+        // in flight (calls, other kernels -> tiled: 464 groups 517.5 -> 539.5 us, 616 23.3 -> 24.0, 720 146 -> 155,
+        // 924 31.7 -> 32.6; 1048 210 -> 183, 1100 40.8 -> 28.4, 1390 27.7 -> 23.0, 2464 653 -> 560, 4376 118 -> 79).
+        // One sample at d = 2048 keeps the pipelined kernel (16384 neurons: both read at the memory's rate, 58.5 against
+        // 59.1 us).  Groups per workgroup: the fewest rounds over the chip, a workgroup counted as 16 groups' time plus
+        // its groups'.
+        const int tblocks = ceil_div(T, kBfTokBlock);
+        const long long groups = static_cast<long long>(n8) * tblocks * B;
+        if (groups >= 4 * kCUs && groups / 12 < (1 << 22) /* grid limit */ &&
+            !(B == 1 && T <= kBfTokBlock && s->d == 2048)) {
+            q.gate_tblocks = tblocks;
+            q.gate_nt = ceil_div(ceil_div(T, tblocks), 16);
+            long long best = -1;
+            for (int t = 1; t <= 12; ++t) {
+                const long long wgs = static_cast<long long>(ceil_div(n8, t)) * tblocks * B;
+                const long long cost = (wgs + kCUs - 1) / kCUs * (16 + t);
+                if (best < 0 || cost <= best) {
+                    best = cost;
+                    q.gate_tiles = t;
+                }
+            }
+            q.gate_blocks = ceil_div(q.kcap / 8, q.gate_tiles);
+        }
         q.col_tile = kBfColTile;
         q.ncol = ceil_div(s->d, q.col_tile);
         const int nchunks = q.kcap / kBfChunk;
@@ -405,6 +429,7 @@ rm_status make_plan(const rm_ffn_shape *s, int B, int T, int max_count, Plan *p,
             // same per-neuron arithmetic and chunk order as the one-launch form's gate/up phase, so a delta step
             // at the anchor's own input finds h - h_a = 0 exactly.
             q.gate_groups = 1;
+            q.gate_tiles = 0;
             q.gate_blocks = kCUs;
             q.gate_spread = (ceil_div(q.kcap / 4, kCUs) + 1) / 2;
         }

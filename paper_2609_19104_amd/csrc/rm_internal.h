@@ -68,7 +68,10 @@ struct Plan {
     int tpad = 0;        // T rounded up to the token block (rows of H)
     int kcap = 0;        // row length of H (neuron slots), max_count rounded up
     int gate_groups = 1; // bf16 gate/up: groups of 8 neurons per workgroup (1 = direct, 2/4/8 = LDS-staged)
-    int gate_blocks = 0; // gate/up workgroups per sample
+    int gate_blocks = 0; // gate/up workgroups per sample (tiled: and token block)
+    int gate_tiles = 0;  // bf16: groups of 8 neurons per workgroup of the tiled gate/up kernel (0 = not used)
+    int gate_nt = 4;     // tiled gate/up: 16-token tiles per token block
+    int gate_tblocks = 1; // tiled gate/up: token blocks
     // bf16, one sample, 257 .. 768 groups of 8 listed slots: the spread gate/up kernel, gate_blocks (= one per
     // compute unit) workgroups taking quads of 4 slots round-robin, in at most gate_spread 16-row tiles each (0 =
     // not used).
