@@ -365,7 +365,7 @@ void gemm_dma_kernel(GemmArgs a) {
             for (int tn = 0; tn < TN; ++tn) {
                 const int n = n0 + wn * TN * 16 + tn * 16 + r;
                 if constexpr (EPI == kEpiGlu) {
-                    const float h = rm_glu_act(a.act, acc[0][tm][tn][i]) * acc[NB - 1][tm][tn][i];
+                    const float h = rm_glu_act_bf16(a.act, acc[0][tm][tn][i]) * acc[NB - 1][tm][tn][i];
                     a.H[blocked_offset(m, n, a.N)] = static_cast<uint16_t>(rm_f32_to_bf16_bits(h));
                 } else if constexpr (EPI == kEpiPartial) {
                     a.part[(static_cast<size_t>(ks_id) * a.m_pad + m) * a.N + n] = acc[0][tm][tn][i];

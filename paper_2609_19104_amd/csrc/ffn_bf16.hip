@@ -171,7 +171,7 @@ __device__ __forceinline__ void gu_store_h(const GuArgs &a, uint16_t *Hb, int b,
             gsum += red(w, tt, lg)[reg];
             usum += red(w, tt, lu)[reg];
         }
-        h = rm_glu_act(a.act, gsum * r) * (usum * r);
+        h = rm_glu_act_bf16(a.act, gsum * r) * (usum * r);
     }
     if (slot < 0) return;
     const int t = t0 + tok;

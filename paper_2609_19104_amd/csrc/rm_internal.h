@@ -339,6 +339,15 @@ __device__ __forceinline__ float rm_gelu_tanh(float z) {
     return 0.5f * z * (1.0f + tanhf(0.7978845608028654f * (z + 0.044715f * z * z * z)));
 }
 
+// The same two for the bf16 kernels, whose h is rounded to bf16: both are z / (1 + e^-w), w = z for SiLU and, since
+// (1 + tanh u) / 2 = 1 / (1 + e^-2u), w = 2 u for GELU; with the hardware's exp2 and reciprocal (within an ulp or
+// two, against h's 8 bits) in place of expf, tanhf and a correctly rounded division.  The tiled gate/up kernel's tail
+// forms 10 h per thread: 16 samples x 18 layers of d = 1024, 1229 of 4096 neurons, 51 tokens 571.7 -> 559.4 us.
+__device__ __forceinline__ float rm_glu_act_bf16(int act, float z) {
+    const float w = act == RM_ACT_GELU_TANH ? 1.5957691216057308f * (z + 0.044715f * z * z * z) : z;
+    return z * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * w));
+}
+
 // The gated linear unit's activation (act: an rm_act).
 __device__ __forceinline__ float rm_glu_act(int act, float z) {
     return act == RM_ACT_GELU_TANH ? rm_gelu_tanh(z) : rm_silu(z);
