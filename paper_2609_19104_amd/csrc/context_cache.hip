@@ -22,8 +22,11 @@
 // 2048 x 16384 weights: 390 FLOP per weight byte, above the bf16 ridge of MI355X), so both run on
 // v_mfma_f32_16x16x32_bf16 with both operands contiguous along K.  On this shape the limit is how fast a compute
 // unit pulls tiles out of L2, not the matrix cores, so the tiles are as large as one workgroup per compute unit
-// allows: 256 rows by 128 columns of each weight matrix (2 MB read per gate/up workgroup over K = 2048), 8 waves
-// each accumulating 64 x 64 per matrix, K staged 64 wide (one cache line per row) straight from memory into LDS.
+// allows: up to 256 rows by 128 columns of each weight matrix (2 MB read per gate/up workgroup over K = 2048), 8 waves,
+// K staged 64 wide (one cache line per row) straight from memory into LDS.  The rows are cut into equal tiles, so that
+// 390 rows take two tiles of 224 and not of 256: gate/up 70.0 -> 64.5 us, down 46.1 -> 42.6 (d = 2048, d_ff = 16384);
+// 144 rows one of 160: the layer 106.9 -> 92.1 us.  Tiles of 256 rows keep 4 waves along the rows x 2 along the columns
+// (2 x 4: 91.4 -> 94.6 us for 492 rows at d_ff = 2176).
 // Workgroups that share a weight tile are numbered onto one XCD so that its L2 serves the re-reads.
 #include "rm_dma.h"
 #include "rm_select.h"
@@ -162,28 +165,29 @@ __global__ __launch_bounds__(256) void pack_blocked_kernel(const uint16_t *__res
 
 // ------------------------------------------------------------------------------------------ gather
 
-// The listed rows of x as bf16 in the blocked layout [m_pad][d]; rows from the count up to m_pad are zero.
+// The listed rows of x as bf16 in the blocked layout [m_pad][d]; rows from the count up to m_pad are zero.  One workgroup
+// per row, two float4 per thread in flight (d = 2048: the whole row): 390 rows 7.2 -> 5.1 us against one wave per
+// row, whose loads went out 1 KB at a time.
 __global__ __launch_bounds__(256) void gather_rows_kernel(const float *__restrict__ x, int d,
                                                           const int32_t *__restrict__ rows,
                                                           const int32_t *__restrict__ count, int max_rows, int m_pad,
                                                           int n_tok, uint16_t *__restrict__ A) {
-    const int i = blockIdx.x * 4 + (threadIdx.x >> 6);  // one wave per row
-    const int lane = threadIdx.x & 63;
-    if (i >= m_pad) return;
+    const int i = blockIdx.x;
     const int cnt = min(max(count[0], 0), max_rows);
-    if (i >= cnt) {
-        for (int c = lane * 4; c < d; c += 256)
-            *reinterpret_cast<uint2 *>(A + blocked_offset(i, c, d)) = make_uint2(0u, 0u);
-        return;
-    }
-    const int r = min(max(rows[i], 0), n_tok - 1);
+    const int r = min(max(rows[min(i, max_rows - 1)], 0), n_tok - 1);
     const float *src = x + static_cast<size_t>(r) * d;
-    for (int c = lane * 4; c < d; c += 256) {
-        const float4 v = *reinterpret_cast<const float4 *>(src + c);
-        uint2 packed;
-        packed.x = rm_f32_to_bf16_bits(v.x) | (rm_f32_to_bf16_bits(v.y) << 16);
-        packed.y = rm_f32_to_bf16_bits(v.z) | (rm_f32_to_bf16_bits(v.w) << 16);
-        *reinterpret_cast<uint2 *>(A + blocked_offset(i, c, d)) = packed;
+    for (int c0 = threadIdx.x * 4; c0 < d; c0 += 2048) {
+        const int c1 = min(c0 + 1024, d - 4);
+        const float4 v[2] = {*reinterpret_cast<const float4 *>(src + c0), *reinterpret_cast<const float4 *>(src + c1)};
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            const int c = c0 + 1024 * k;
+            uint2 packed;
+            packed.x = rm_f32_to_bf16_bits(v[k].x) | (rm_f32_to_bf16_bits(v[k].y) << 16);
+            packed.y = rm_f32_to_bf16_bits(v[k].z) | (rm_f32_to_bf16_bits(v[k].w) << 16);
+            if (i >= cnt) packed = make_uint2(0u, 0u);
+            if (c < d) *reinterpret_cast<uint2 *>(A + blocked_offset(i, c, d)) = packed;
+        }
     }
 }
 
@@ -194,7 +198,7 @@ enum { kEpiGlu = 0, kEpiScatter = 1, kEpiPartial = 2 };
 struct GemmArgs {
     const uint16_t *A;       // bf16 [m_pad][K], blocked
     const uint16_t *B0, *B1; // bf16 [N][K], row-major or blocked (B1: the up matrix of the gate/up product)
-    int K, N, m_pad;
+    int K, N, m_pad, mt;     // mt: row tiles
     const int32_t *count;    // rows of A in use (device), clamped to [0, max_rows]
     int max_rows, act;
     uint16_t *H;             // kEpiGlu: bf16 [m_pad][N], blocked
@@ -214,29 +218,20 @@ struct GemmArgs {
 // so each load reads 1 KB of consecutive memory; a row-major B is read 128 bytes per row, each lane taking the
 // piece that belongs at its position.
 
-// Waves per SIMD that the stage buffers allow (160 KB of LDS per compute unit), at most 2: the register budget
-// follows from it.
-constexpr int dma_waves_per_simd(int lds_bytes, int waves) {
-    return (163840 / lds_bytes) * waves / 4 >= 2 ? 2 : 1;
-}
-
-template <int TM, int TN, int NB, int STAGES, int WAVES_M, bool B_BLOCKED, int EPI>
-__global__ __launch_bounds__(128 * WAVES_M,
-                             dma_waves_per_simd(STAGES * (16 * WAVES_M * TM + NB * 32 * TN) * kRowBytes, 2 * WAVES_M))
-void gemm_dma_kernel(GemmArgs a) {
-    constexpr int WAVES = 2 * WAVES_M;             // WAVES_M x 2 waves, each (16 TM) x (16 TN) per matrix
-    constexpr int BM = 16 * WAVES_M * TM, BN = 32 * TN;
+template <int WAVES_M, int TM, int TN, int NB, int STAGES, bool B_BLOCKED, int EPI>
+__global__ __launch_bounds__(512, 2) void gemm_dma_kernel(GemmArgs a) {
+    constexpr int WAVES = 8, WAVES_N = WAVES / WAVES_M;  // each wave (16 TM) x (16 TN) per matrix
+    constexpr int BM = 16 * WAVES_M * TM, BN = 16 * WAVES_N * TN;
     constexpr int ROWS = BM + NB * BN;             // a stage: BM rows of A, then BN rows of each B matrix
     constexpr int RPB = 1024 / kRowBytes;          // rows per 1 KB load block
-    static_assert(ROWS % (WAVES * RPB) == 0 && BM % (WAVES * RPB) == 0, "load blocks must split evenly");
-    static_assert(BM % 64 == 0 && BN % 64 == 0, "tiles of whole 64-row blocks");
-    constexpr int BPW = ROWS / RPB / WAVES;        // load blocks per wave and stage
-    constexpr int JA = BM / RPB / WAVES;           // the wave's first JA load blocks are rows of A
+    static_assert(BM % 16 == 0 && BN % 64 == 0 && ROWS % RPB == 0, "whole load blocks");
+    constexpr int BLOCKS = ROWS / RPB;
+    constexpr int BPW = (BLOCKS + WAVES - 1) / WAVES;  // load blocks per wave and stage (past the last: dummies)
     static_assert(STAGES >= 2 && STAGES <= 4 && BPW * (STAGES - 2) <= 63, "vmcnt range");
-    constexpr int STAGE = ROWS * kRowBytes;
+    constexpr int STAGE = BPW * WAVES * 1024;
     __shared__ __attribute__((aligned(1024))) uint8_t lds[STAGES][STAGE];
 
-    const int mt = a.m_pad / BM;
+    const int mt = a.mt;
     const int ntl = a.N / BN;
     // q = (K slice * ntl + n tile) * mt + m tile: the tiles of one K slice share an XCD (so its L2 holds the slice
     // of A that they all read), and the m tiles of one n tile are neighbours (sharing the weight rows).
@@ -251,7 +246,7 @@ void gemm_dma_kernel(GemmArgs a) {
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
-    const int wave = tid >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave % WAVES_M, wn = wave / WAVES_M;
     const int r = lane & 15, grp = lane >> 4;
 
@@ -259,21 +254,22 @@ void gemm_dma_kernel(GemmArgs a) {
     // blocked operand advances one 8 KB block per stage, a row-major one 128 bytes.
     const size_t kblocks = static_cast<size_t>(a.K / kStageK), kb0 = static_cast<size_t>(k_base / kStageK);
     const uint16_t *src[BPW];
+    auto is_a = [&](int j) { return (wave + WAVES * j) * RPB < BM; };
+    auto is_real = [&](int j) { return wave + WAVES * j < BLOCKS; };  // a dummy reads the matrix's first piece
 #pragma unroll
     for (int j = 0; j < BPW; ++j) {
         const int row = (wave + WAVES * j) * RPB;  // first stage row of the block
-        const uint16_t *base;
-        int mrow;
-        if (j < JA) {
-            base = a.A;
-            mrow = m0 + row;
-        } else {
+        const uint16_t *base = a.A;
+        int mrow = m0 + row;
+        if (!is_a(j)) {
             const int rb = row - BM;
             const int nb = rb / BN;
             base = nb ? a.B1 : a.B0;
             mrow = n0 + rb - nb * BN;
         }
-        if (j < JA || B_BLOCKED) {
+        if (!is_real(j)) {
+            src[j] = a.A;
+        } else if (is_a(j) || B_BLOCKED) {
             src[j] = base + ((mrow >> 6) * kblocks + kb0) * kBlockElems + (mrow & 63) * kStageK + lane * 8;
         } else {
             constexpr int kPieces = kStageK / 8;
@@ -287,7 +283,7 @@ void gemm_dma_kernel(GemmArgs a) {
         const uint32_t buf = lds0 + (kt % STAGES) * STAGE;
 #pragma unroll
         for (int j = 0; j < BPW; ++j) {
-            const size_t step = (j < JA || B_BLOCKED) ? kBlockElems : kStageK;
+            const size_t step = !is_real(j) ? 0 : (is_a(j) || B_BLOCKED) ? kBlockElems : kStageK;
             dma16(src[j] + static_cast<size_t>(kt) * step,
                   __builtin_amdgcn_readfirstlane(buf + (wave + WAVES * j) * 1024));
         }
@@ -388,12 +384,23 @@ __global__ __launch_bounds__(256) void reduce_scatter_kernel(const float *__rest
     const int i = static_cast<int>(e / per_row);
     if (i >= cnt) return;
     const int c = static_cast<int>(e - static_cast<long long>(i) * per_row) * 4;
-    float4 s = *reinterpret_cast<const float4 *>(part + static_cast<size_t>(i) * N + c);
-    for (int k = 1; k < splits; ++k) {
-        const float4 v = *reinterpret_cast<const float4 *>(part + (static_cast<size_t>(k) * m_pad + i) * N + c);
-        s = make_float4(s.x + v.x, s.y + v.y, s.z + v.z, s.w + v.w);
-    }
+    // Eight slices' loads in flight with the row's (slices past the last re-read it and are not added): 144 rows
+    // at d = 2048 93.0 -> 91.9 us per layer, 390 rows the same.
     const int row = min(max(rows[i], 0), n_tok - 1);
+    float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int k0 = 0; k0 < splits; k0 += 8) {
+        float4 v[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+            v[k] = *reinterpret_cast<const float4 *>(
+                part + (static_cast<size_t>(min(k0 + k, splits - 1)) * m_pad + i) * N + c);
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+            if (k0 + k == 0)
+                s = v[0];
+            else if (k0 + k < splits)
+                s = make_float4(s.x + v[k].x, s.y + v[k].y, s.z + v[k].z, s.w + v[k].w);
+    }
     *reinterpret_cast<float4 *>(y + static_cast<size_t>(row) * N + c) = s;
 }
 
@@ -418,12 +425,37 @@ hipError_t launch_context_select(const float *x, const float *x_ref, int n_tok, 
     return hipGetLastError();
 }
 
+// WM waves along the rows, TM x 16 rows each: row tiles of 16 WM TM.
+template <bool B_BLOCKED, int WM, int TM>
+static hipError_t context_gemms_tm(const ContextPlan &p, const GemmArgs &g, const GemmArgs &o, hipStream_t st) {
+    constexpr int TN = WM;  // 128 columns over 8 / WM waves
+    const dim3 block(512);
+    hipError_t e = launch_timed(RM_KERNEL_GATEUP, gemm_dma_kernel<WM, TM, TN, 2, RM_CTX_GLU_STAGES, B_BLOCKED, kEpiGlu>,
+                                dim3(p.mt * (p.d_ff / kCtxGluBN)), block, st, g);
+    if (e == hipSuccess) e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    const dim3 grid(p.mt * (p.d / p.down_bn) * p.down_splits);
+    constexpr int S = RM_CTX_DOWN_STAGES;
+    // Split over K: the slices' float32 partials, whose ordered sum is then scattered into y.
+    const bool wide = p.down_bn == 128, split = p.down_splits > 1;
+    if (wide)
+        e = split ? launch_timed(RM_KERNEL_DOWN, gemm_dma_kernel<WM, TM, TN, 1, S, B_BLOCKED, kEpiPartial>, grid,
+                                 block, st, o)
+                  : launch_timed(RM_KERNEL_DOWN, gemm_dma_kernel<WM, TM, TN, 1, S, B_BLOCKED, kEpiScatter>, grid,
+                                 block, st, o);
+    else
+        e = split ? launch_timed(RM_KERNEL_DOWN, gemm_dma_kernel<WM, TM, TN / 2, 1, S, B_BLOCKED, kEpiPartial>, grid,
+                                 block, st, o)
+                  : launch_timed(RM_KERNEL_DOWN, gemm_dma_kernel<WM, TM, TN / 2, 1, S, B_BLOCKED, kEpiScatter>, grid,
+                                 block, st, o);
+    return e != hipSuccess ? e : hipGetLastError();
+}
+
 template <bool B_BLOCKED>
 static hipError_t context_gemms(const ContextPlan &p, const uint16_t *w_gate, const uint16_t *w_up,
                                 const uint16_t *w_down_t, const int32_t *rows, const int32_t *count, float *y,
                                 char *base, hipStream_t st) {
-    constexpr int kWavesM = kCtxBM / 64;
-    static_assert(kCtxGluBN == 128, "gate/up tiles of 4 x 16 neurons per wave");
+    static_assert(kCtxGluBN == 128, "gate/up tiles of 8 x 16 neurons");
     uint16_t *H = reinterpret_cast<uint16_t *>(base + p.off_h);
     GemmArgs g{};
     g.A = reinterpret_cast<const uint16_t *>(base + p.off_a);
@@ -432,16 +464,12 @@ static hipError_t context_gemms(const ContextPlan &p, const uint16_t *w_gate, co
     g.K = p.d;
     g.N = p.d_ff;
     g.m_pad = p.m_pad;
+    g.mt = p.mt;
     g.count = count;
     g.max_rows = p.max_rows;
     g.act = p.act;
     g.H = H;
     g.splits = 1;
-    hipError_t e =
-        launch_timed(RM_KERNEL_GATEUP, gemm_dma_kernel<4, 4, 2, RM_CTX_GLU_STAGES, kWavesM, B_BLOCKED, kEpiGlu>,
-                     dim3((p.m_pad / kCtxBM) * (p.d_ff / kCtxGluBN)), dim3(128 * kWavesM), st, g);
-    if (e == hipSuccess) e = hipGetLastError();
-    if (e != hipSuccess) return e;
 
     GemmArgs o{};
     o.A = H;
@@ -450,6 +478,7 @@ static hipError_t context_gemms(const ContextPlan &p, const uint16_t *w_gate, co
     o.K = p.d_ff;
     o.N = p.d;
     o.m_pad = p.m_pad;
+    o.mt = p.mt;
     o.count = count;
     o.max_rows = p.max_rows;
     o.y = y;
@@ -457,23 +486,15 @@ static hipError_t context_gemms(const ContextPlan &p, const uint16_t *w_gate, co
     o.n_tok = p.n_tok;
     o.splits = p.down_splits;
     o.part = reinterpret_cast<float *>(base + p.off_part);  // used when split
-    const dim3 grid((p.m_pad / kCtxBM) * (p.d / p.down_bn) * p.down_splits), block(128 * kWavesM);
-    constexpr int S = RM_CTX_DOWN_STAGES;
-    const bool wide = p.down_bn == 128;
-    if (p.down_splits == 1) {
-        e = wide ? launch_timed(RM_KERNEL_DOWN, gemm_dma_kernel<4, 4, 1, S, kWavesM, B_BLOCKED, kEpiScatter>, grid,
-                                block, st, o)
-                 : launch_timed(RM_KERNEL_DOWN, gemm_dma_kernel<4, 2, 1, S, kWavesM, B_BLOCKED, kEpiScatter>, grid,
-                                block, st, o);
-        return e != hipSuccess ? e : hipGetLastError();
+    hipError_t e;
+    switch (p.tm) {
+        case 4: e = context_gemms_tm<B_BLOCKED, 2, 4>(p, g, o, st); break;
+        case 5: e = context_gemms_tm<B_BLOCKED, 2, 5>(p, g, o, st); break;
+        case 6: e = context_gemms_tm<B_BLOCKED, 2, 6>(p, g, o, st); break;
+        case 7: e = context_gemms_tm<B_BLOCKED, 2, 7>(p, g, o, st); break;
+        default: e = context_gemms_tm<B_BLOCKED, 4, 4>(p, g, o, st); break;
     }
-    // Split over K: the slices' float32 partials, then their ordered sum scattered into y.
-    e = wide ? launch_timed(RM_KERNEL_DOWN, gemm_dma_kernel<4, 4, 1, S, kWavesM, B_BLOCKED, kEpiPartial>, grid, block,
-                            st, o)
-             : launch_timed(RM_KERNEL_DOWN, gemm_dma_kernel<4, 2, 1, S, kWavesM, B_BLOCKED, kEpiPartial>, grid, block,
-                            st, o);
-    if (e == hipSuccess) e = hipGetLastError();
-    if (e != hipSuccess) return e;
+    if (e != hipSuccess || p.down_splits == 1) return e;
     const long long n4 = static_cast<long long>(p.max_rows) * (p.d / 4);
     hipLaunchKernelGGL(reduce_scatter_kernel, dim3(static_cast<unsigned>((n4 + 255) / 256)), dim3(256), 0, st,
                        static_cast<const float *>(o.part), p.down_splits, p.m_pad, p.d, rows, count, p.max_rows,
@@ -485,7 +506,7 @@ hipError_t launch_context_ffn(const ContextPlan &p, const void *w_gate, const vo
                               bool blocked, const float *x, const int32_t *rows, const int32_t *count, float *y,
                               void *ws, hipStream_t st) {
     char *base = static_cast<char *>(ws);
-    hipLaunchKernelGGL(gather_rows_kernel, dim3((p.m_pad + 3) / 4), dim3(256), 0, st, x, p.d, rows, count,
+    hipLaunchKernelGGL(gather_rows_kernel, dim3(p.m_pad), dim3(256), 0, st, x, p.d, rows, count,
                        p.max_rows, p.m_pad, p.n_tok, reinterpret_cast<uint16_t *>(base + p.off_a));
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;

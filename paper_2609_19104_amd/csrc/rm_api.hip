@@ -837,6 +837,9 @@ static rm_status context_plan(const rm_ffn_shape *s, int n_tok, int max_rows, rm
     q.n_tok = n_tok;
     q.max_rows = max_rows;
     q.m_pad = ceil_div(max_rows, rm::kCtxBM) * rm::kCtxBM;
+    // The rows in equal tiles of at most 256, rounded to 32 (390 rows: two tiles of 224 instead of 256).
+    q.mt = q.m_pad / rm::kCtxBM;
+    q.tm = std::max(4, ceil_div(ceil_div(max_rows, q.mt), 32));
     q.down_bn = rm::ctx_down_bn(s->d);
     const long long tiles = static_cast<long long>(q.m_pad / rm::kCtxBM) * (s->d_ff / rm::kCtxGluBN);
     if (tiles > 0x7fffffffLL) return fail(RM_ERR_SHAPE, "launch grid too large");

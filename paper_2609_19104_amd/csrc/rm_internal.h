@@ -124,9 +124,8 @@ hipError_t launch_gather_rows(const rm_ffn_layer_weights *w, const int32_t *idx,
 
 // Context Cache (context_cache.hip).  Workspace plan: the gathered rows as bf16 [m_pad][d], then H bf16
 // [m_pad][d_ff] (both in the GEMMs' blocked layout), then the down GEMM's K-slice partials; m_pad = max_rows
-// rounded up to the row tile.  GEMM tiles: 256 rows by 8 waves (4 along the rows x 2 along the columns), each wave
-// 64 rows x 64 columns per weight matrix; the gate/up tile spans 128 neurons of both matrices, the down tile 128
-// output columns (64 when d is not a multiple of 128).  The stage counts and the down GEMM's workgroup target can
+// rounded up to 256.  GEMM tiles: 32 tm rows (tm 4 to 8: the rows in equal tiles of at most 256) by 8 waves (2 along the
+// rows x 4 along the columns, or 4 x 2 at tm = 8); the gate/up tile spans 128 neurons of both matrices, the down tile 128 output columns (64 when d is not a multiple of 128).  The stage counts and the down GEMM's workgroup target can
 // be set at build time (RM_CTX_GLU_STAGES, RM_CTX_DOWN_STAGES, RM_CTX_DOWN_TARGET) for tuning sweeps.
 #ifndef RM_CTX_GLU_STAGES
 #define RM_CTX_GLU_STAGES 2
@@ -143,6 +142,7 @@ constexpr int kCtxDownTarget = RM_CTX_DOWN_TARGET;  // down: workgroups the K sp
 inline int ctx_down_bn(int d) { return d % 128 == 0 ? 128 : 64; }
 struct ContextPlan {
     int d = 0, d_ff = 0, act = 0, n_tok = 0, max_rows = 0, m_pad = 0;
+    int mt = 1, tm = 8;   // row tiles of 32 tm rows (mt * 32 tm <= m_pad)
     int down_bn = 128;    // output columns per down tile
     int down_splits = 1;  // K slices of the down GEMM (float32 partials [splits][m_pad][d] when > 1)
     size_t off_a = 0, off_h = 0, off_part = 0, total = 0;

@@ -123,10 +123,15 @@ FFN_CASES = [
     (256, 1024, 200, 0, 200, 199, 200, "gelu_tanh"),
     (64, 128, 30, 0, 30, 0, 5, "gelu_tanh"),
 ]
+# Row tiles of 128, 160, 192, 224 and 256 rows, at their last row and one past, one to three of them; the down product
+# split over K (d_ff = 2048) and not, 128 and 64 columns wide.
+TILE_CASES = [(d, d_ff, n, 0, n, n, n, "silu") for d, d_ff, n in
+              [(128, 256, 128), (128, 2048, 129), (192, 128, 161), (192, 2048, 193), (128, 256, 225), (128, 2048, 256),
+               (128, 128, 257), (192, 2048, 390), (128, 256, 449), (64, 128, 513), (128, 2048, 768)]]
 
 
 @pytest.mark.parametrize("packed", [False, True], ids=["row-major", "packed"])
-@pytest.mark.parametrize("d,d_ff,n_tok,v0,P,k,max_rows,act", FFN_CASES)
+@pytest.mark.parametrize("d,d_ff,n_tok,v0,P,k,max_rows,act", FFN_CASES + TILE_CASES)
 def test_context_ffn_parity(d, d_ff, n_tok, v0, P, k, max_rows, act, packed):
     w = wl.context_workload(n_tok=n_tok, v0=v0, P=P, d=d, d_ff=d_ff, seed=7 + d)
     drift = cc.drift(w.x[v0:v0 + P], w.x_ref[v0:v0 + P])
