@@ -62,6 +62,15 @@ __device__ __forceinline__ rm_u32x4 zero16() { return rm_u32x4{0u, 0u, 0u, 0u}; 
 __device__ __forceinline__ int clamp_neuron(int n, int d_ff) { return n < 0 ? 0 : (n >= d_ff ? d_ff - 1 : n); }
 __device__ __forceinline__ int clamp_count(int c, int max_count) { return c < 0 ? 0 : (c > max_count ? max_count : c); }
 
+// H is [slot / 8][token][8 slots]: element offset of (slot, token t).  16 lanes of a down projection's fragment load (8
+// slots of 16 tokens) are then 256 consecutive bytes, which the L1 looks up as 4 pieces; as [chunk of 32][token][32
+// slots] they were 16 pieces 64 bytes apart, and those lookups were most of the fused down kernel's at 16 samples.
+// 16 samples x 18 layers (d = 1024, 1229 of 4096 neurons, T = 51) 561.7 -> 552.6 us, 18 dense anchor layers 444.2 -> 434.7,
+// 5 ragged samples of d = 768 23.1 -> 22.4.
+__device__ __forceinline__ size_t h_at(int slot, int t, int tpad) {
+    return (static_cast<size_t>(slot >> 3) * tpad + t) * 8 + (slot & 7);
+}
+
 // Workgroups are dispatched to the 8 XCDs in turn (workgroup i to XCD i mod 8), each XCD with its own L2.  The
 // logical index of workgroup `id` of `n` numbers the workgroups so that logical indices [k a, (k + 1) a) (about
 // n / 8 of them) run on XCD k: consecutive logical indices share an L2.  The kernels put the samples of one
@@ -149,8 +158,8 @@ __device__ __forceinline__ int lane_neuron(const GuArgs &a, int b, int slot) {
 // ------------------------------------------------------------------------------------------ gate / up, direct
 
 // Writes h for 8 neurons x 64 tokens of token block t0 from the summed tile; slots at or past the count and
-// tokens at or past T get h = 0 (their rows and columns were computed from clamped loads).  H is chunk-major
-// (32-slot chunks, then tokens).  Thread tid finishes tile row tid & 7 (its gate row; the up row is 8 further) for
+// tokens at or past T get h = 0 (their rows and columns were computed from clamped loads).  Thread tid finishes tile
+// row tid & 7 (its gate row; the up row is 8 further) for
 // token tid >> 3, whose list slot is `slot` (< 0: a duplicate row, nothing stored) and RMSNorm factor r.
 // ha_pre: the Eq. 4 anchor value was loaded ahead (ha, from anchor_h), else it is loaded here.
 // red(w, tt, lane) is d-part w's tile tt (lane L, register i = row 4 (L / 16) + i, token L % 16).
@@ -183,8 +192,7 @@ __device__ __forceinline__ void gu_store_h(const GuArgs &a, uint16_t *Hb, int b,
     }
     if (a.h_anchor != nullptr && live) h -= ha_pre ? ha : a.h_anchor[ai];  // Eq. 4: h_t - h_a, rounded once
     if (!live) h = 0.0f;
-    Hb[(static_cast<size_t>(slot >> 5) * a.tpad + t) * rm::kBfChunk + (slot & 31)] =
-        static_cast<uint16_t>(rm_f32_to_bf16_bits(h));
+    Hb[h_at(slot, t, a.tpad)] = static_cast<uint16_t>(rm_f32_to_bf16_bits(h));
 }
 
 // Geometry of the direct kernel's per-wave column slice: SPW K steps of 32 columns, staged in sub-slices of at
@@ -326,8 +334,7 @@ __global__ __launch_bounds__(kGuThreads) void gateup_staged_kernel(GuArgs a) {
         if (a.h_out != nullptr) return;
         for (int e = tid; e < a.tpad * NG; e += kGuThreads) {
             const int t = e / NG, slot = blk0 + (e % NG) * 8;
-            *reinterpret_cast<rm_u32x4 *>(Hb + (static_cast<size_t>(slot >> 5) * a.tpad + t) * rm::kBfChunk +
-                                          (slot & 31)) = zero16();
+            *reinterpret_cast<rm_u32x4 *>(Hb + h_at(slot, t, a.tpad)) = zero16();
         }
         return;
     }
@@ -438,8 +445,7 @@ __global__ __launch_bounds__(kGuThreads) void gateup_staged_unrolled_kernel(GuAr
         if (a.h_out != nullptr) return;
         for (int e = tid; e < a.tpad * NG; e += kGuThreads) {
             const int t = e / NG, slot = blk0 + (e % NG) * 8;
-            *reinterpret_cast<rm_u32x4 *>(Hb + (static_cast<size_t>(slot >> 5) * a.tpad + t) * rm::kBfChunk +
-                                          (slot & 31)) = zero16();
+            *reinterpret_cast<rm_u32x4 *>(Hb + h_at(slot, t, a.tpad)) = zero16();
         }
         return;
     }
@@ -684,8 +690,7 @@ __global__ __launch_bounds__(kGuThreads, 2) void gateup_tile_kernel(GuArgs a, in
         for (int e = tid; e < 16 * NT * tiles; e += kGuThreads) {
             const int t = t0 + e / tiles, slot = slot0 + (e % tiles) * 8;
             if (slot < a.kcap)
-                *reinterpret_cast<rm_u32x4 *>(Hb + (static_cast<size_t>(slot >> 5) * a.tpad + t) * rm::kBfChunk +
-                                              (slot & 31)) = zero16();
+                *reinterpret_cast<rm_u32x4 *>(Hb + h_at(slot, t, a.tpad)) = zero16();
         }
         return;
     }
@@ -1074,8 +1079,8 @@ __global__ __launch_bounds__(kDnThreads) void down_bf16_kernel(DnArgs a) {
     auto load_h = [&](DnChunk<NT> &cc, int k, int t0) {
         const int ce = chunk_of(k);
 #pragma unroll
-        for (int tt = 0; tt < NT; ++tt)  // chunk-major H: 16 tokens x 64 bytes, one contiguous kilobyte
-            cc.a[tt] = load16(Hb + (static_cast<size_t>(ce) * a.tpad + t0 + tt * 16 + nn) * rm::kBfChunk + grp * 8);
+        for (int tt = 0; tt < NT; ++tt)
+            cc.a[tt] = load16(Hb + h_at(ce * rm::kBfChunk + grp * 8, t0 + tt * 16 + nn, a.tpad));
     };
     auto load_w = [&](DnChunk<NT> &cc, int k) {
         const int kb = (chunk_of(k) - c_begin) * rm::kBfChunk + grp * 8;
@@ -1477,7 +1482,7 @@ __global__ __launch_bounds__(kGuThreads) void layer_xcd_kernel(XlArgs a) {
         const int ce = chunk_of(k);
 #pragma unroll
         for (int tt = 0; tt < NT; ++tt)
-            cb[k].a[tt] = load16(g.H + (static_cast<size_t>(ce) * g.tpad + tt * 16 + nn) * rm::kBfChunk + grp * 8);
+            cb[k].a[tt] = load16(g.H + h_at(ce * rm::kBfChunk + grp * 8, tt * 16 + nn, g.tpad));
 #pragma unroll
         for (int j = 0; j < 8; ++j) cb[k].w[j] = wdn[k][j];
     }
@@ -1600,16 +1605,14 @@ __global__ __launch_bounds__(kDfThreads) void down_fused_kernel(DfArgs a) {
 
     auto chunk_of = [&](int k) { return min(wave + k * rm::kDfWaves, nchunks - 1); };
     DnChunk<NT> cb[CPS];
-    auto load_h = [&](int stage) {  // chunk-major H: 16 tokens x 64 bytes, one contiguous kilobyte per tile
+    auto load_h = [&](int stage) {
 #pragma unroll
         for (int k = 0; k < CPS; ++k)
             if (stage * CPS + k < CPW)
 #pragma unroll
                 for (int j = 0; j < NT; ++j)
-                    cb[k].a[j] = load16(Hb +
-                                        (static_cast<size_t>(chunk_of(stage * CPS + k)) * a.tpad + t0 + j * 16 + nn) *
-                                            rm::kBfChunk +
-                                        grp * 8);
+                    cb[k].a[j] = load16(
+                        Hb + h_at(chunk_of(stage * CPS + k) * rm::kBfChunk + grp * 8, t0 + j * 16 + nn, a.tpad));
     };
     load_h(0);
 #pragma unroll

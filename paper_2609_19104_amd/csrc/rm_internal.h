@@ -94,7 +94,7 @@ struct Plan {
     // launch (layer_xcd_kernel) that reads the float32 input itself, slices = the 8 XCDs' slices of slice_units
     // chunks; no prologue launch, the epilogue follows.
     bool xcd_layer = false;
-    // Workspace: xn [B][T][d] (bf16; the f32 kernels read x itself); H, chunk-major (bf16: [B][kcap / 32][tpad][32];
+    // Workspace: xn [B][T][d] (bf16; the f32 kernels read x itself); H (bf16: [B][kcap / 8][tpad][8];
     // f32: [B][kcap / 16][T][16]); partials f32 [B][slices][T][d]; ssq f32 [B][T][ssq_stride(d)]
     // (per-token sums of squares of the FFN input by 32-column block, for the RMSNorm factor); and, for the dense
     // reference, the lists 0 .. d_ff-1 int32 [B][d_ff] and their counts int32 [B].
