@@ -37,12 +37,31 @@ __global__ __launch_bounds__(rm_units::kCompactThreads) void compact_prologue_ke
     if (unit < units) rm_units::prologue_unit(x, g, d, nblk, xn, ssq, unit, threadIdx.x & 63);
 }
 
-__global__ __launch_bounds__(256) void identity_lists_kernel(int32_t *idx, int32_t *count, int d_ff, int B) {
+// The lists 0 .. d_ff-1 and counts d_ff of B samples, by `groups` workgroups of 256 threads, this one the w-th.
+__device__ __forceinline__ void identity_lists(int32_t *idx, int32_t *count, int d_ff, int B, int w, int groups) {
     const size_t n = static_cast<size_t>(B) * d_ff;
-    const size_t step = static_cast<size_t>(gridDim.x) * 256;
-    for (size_t i = static_cast<size_t>(blockIdx.x) * 256 + threadIdx.x; i < n; i += step)
-        idx[i] = static_cast<int32_t>(i % d_ff);
-    for (int b = threadIdx.x; blockIdx.x == 0 && b < B; b += 256) count[b] = d_ff;
+    const size_t step = static_cast<size_t>(groups) * 256;
+    for (size_t i = static_cast<size_t>(w) * 256 + threadIdx.x; i < n; i += step) idx[i] = static_cast<int32_t>(i % d_ff);
+    for (int b = threadIdx.x; w == 0 && b < B; b += 256) count[b] = d_ff;
+}
+
+__global__ __launch_bounds__(256) void identity_lists_kernel(int32_t *idx, int32_t *count, int d_ff, int B) {
+    identity_lists(idx, count, d_ff, B, blockIdx.x, gridDim.x);
+}
+
+// The identity lists and the prologue in one launch (they are independent), as the compaction and the prologue:
+// workgroups [0, n_lists) write the lists, each later one runs four prologue units.
+__global__ __launch_bounds__(256) void identity_prologue_kernel(int32_t *idx, int32_t *count, int d_ff, int B,
+                                                                int n_lists, const float *__restrict__ x,
+                                                                const float *__restrict__ g, int d, int nblk, int units,
+                                                                uint16_t *__restrict__ xn, float *__restrict__ ssq) {
+    const int w = static_cast<int>(blockIdx.x);
+    if (w < n_lists) {
+        identity_lists(idx, count, d_ff, B, w, n_lists);
+        return;
+    }
+    const int unit = (w - n_lists) * 4 + static_cast<int>(threadIdx.x >> 6);
+    if (unit < units) rm_units::prologue_unit(x, g, d, nblk, xn, ssq, unit, threadIdx.x & 63);
 }
 
 }  // namespace
@@ -56,6 +75,20 @@ hipError_t launch_identity_lists(const Plan &p, void *ws, hipStream_t st) {
     const size_t n = static_cast<size_t>(p.B) * p.d_ff;
     const int blocks = static_cast<int>(std::min<size_t>((n + 255) / 256, 1024));
     hipLaunchKernelGGL(identity_lists_kernel, dim3(blocks), dim3(256), 0, st, idx, count, p.d_ff, p.B);
+    return hipGetLastError();
+}
+
+hipError_t launch_identity_prologue(const Plan &p, const float *x, const float *norm_g, void *ws, hipStream_t st) {
+    char *base = static_cast<char *>(ws);
+    int32_t *idx = reinterpret_cast<int32_t *>(base + p.off_ident);
+    int32_t *count = reinterpret_cast<int32_t *>(base + p.off_ident_count);
+    const size_t n = static_cast<size_t>(p.B) * p.d_ff;
+    const int n_lists = static_cast<int>(std::min<size_t>((n + 255) / 256, 1024));
+    const int nblk = (p.d + kRowBlock - 1) / kRowBlock;
+    const int units = p.B * p.T * nblk;
+    hipLaunchKernelGGL(identity_prologue_kernel, dim3(n_lists + (units + 3) / 4), dim3(256), 0, st, idx, count, p.d_ff,
+                       p.B, n_lists, x, norm_g, p.d, nblk, units, reinterpret_cast<uint16_t *>(base + p.off_xn),
+                       reinterpret_cast<float *>(base + p.off_ssq));
     return hipGetLastError();
 }
 

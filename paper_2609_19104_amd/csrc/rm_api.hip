@@ -207,11 +207,12 @@ struct AnchorTerms {
 
 // Layers 0..L-1 of one call; w[l] are the layers' weights, lists at idx + l * list_stride and counts at
 // count + l * count_stride (both strides 0 when every layer uses the same lists, as the dense calls do).
-// A non-null mask ([n_masks][d_ff]) is compacted into idx / count in the prologue's launch.
+// A non-null mask ([n_masks][d_ff]) is compacted into idx / count in the prologue's launch; with `identity` (the dense
+// calls) that launch writes the workspace's identity lists instead, which idx / count point to.
 rm_status run_layers(const rm::Plan &p, const rm_ffn_layer_weights *w, int L, const float *x, float *y,
                      const int32_t *idx, const int32_t *count, size_t list_stride, size_t count_stride, void *ws,
                      hipStream_t st, const AnchorTerms &at = AnchorTerms{}, const uint8_t *mask = nullptr,
-                     int n_masks = 0) {
+                     int n_masks = 0, bool identity = false) {
     // The one-launch layer form and the float32 kernels read the float32 input themselves: only a mask's
     // compaction precedes them.
     const bool bf = p.wdtype == RM_BF16;
@@ -219,6 +220,9 @@ rm_status run_layers(const rm::Plan &p, const rm_ffn_layer_weights *w, int L, co
     if (p.xcd_layer || !bf) {
         if (mask) e = rm::launch_mask_compact(mask, n_masks, p.d_ff, const_cast<int32_t *>(idx),
                                               const_cast<int32_t *>(count), st);
+        if (identity) e = rm::launch_identity_lists(p, ws, st);
+    } else if (identity) {
+        e = rm::launch_identity_prologue(p, x, w[0].norm_g, ws, st);
     } else {
         e = mask ? rm::launch_compact_prologue(p, mask, n_masks, const_cast<int32_t *>(idx),
                                                const_cast<int32_t *>(count), x, w[0].norm_g, ws, st)
@@ -693,11 +697,10 @@ RM_EXPORT rm_status rm_dense_ffn_ref(const rm_ffn_shape *s, const rm_ffn_layer_w
     st = check_gates(w, 1, B, T, s->d, y);
     if (st != RM_OK) return st;
     const hipStream_t hs = static_cast<hipStream_t>(stream);
-    const hipError_t e = rm::launch_identity_lists(p, ws, hs);
-    if (e != hipSuccess) return hip_fail(e, "identity list launch");
     char *base = static_cast<char *>(ws);
     st = run_layers(p, w, 1, x, y, reinterpret_cast<const int32_t *>(base + p.off_ident),
-                    reinterpret_cast<const int32_t *>(base + p.off_ident_count), 0, 0, ws, hs);
+                    reinterpret_cast<const int32_t *>(base + p.off_ident_count), 0, 0, ws, hs, AnchorTerms{}, nullptr,
+                    0, true);
     return st == RM_OK ? ok() : st;
 }
 
@@ -731,11 +734,9 @@ RM_EXPORT rm_status rm_anchor_ffn_stack(const rm_ffn_shape *s, const rm_ffn_laye
     at.cap_plan = &q;
     at.h_stride = static_cast<size_t>(B) * max_count * T;
     const hipStream_t hs = static_cast<hipStream_t>(stream);
-    const hipError_t e = rm::launch_identity_lists(p, ws, hs);
-    if (e != hipSuccess) return hip_fail(e, "identity list launch");
     char *base = static_cast<char *>(ws);
     st = run_layers(p, w, L, x, y, reinterpret_cast<const int32_t *>(base + p.off_ident),
-                    reinterpret_cast<const int32_t *>(base + p.off_ident_count), 0, 0, ws, hs, at);
+                    reinterpret_cast<const int32_t *>(base + p.off_ident_count), 0, 0, ws, hs, at, nullptr, 0, true);
     return st == RM_OK ? ok() : st;
 }
 

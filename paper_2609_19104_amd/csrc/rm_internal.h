@@ -170,6 +170,10 @@ hipError_t launch_identity_lists(const Plan &p, void *ws, hipStream_t st);
 // squares.
 hipError_t launch_prologue(const Plan &p, const float *x, const float *norm_g, void *ws, hipStream_t st);
 
+// launch_identity_lists and launch_prologue in one launch (dense d = 2048, d_ff = 16384: 58.5 us with two
+// launches, 56.6 with one).
+hipError_t launch_identity_prologue(const Plan &p, const float *x, const float *norm_g, void *ws, hipStream_t st);
+
 // rm_mask_compact of n_masks masks and launch_prologue in one launch.
 hipError_t launch_compact_prologue(const Plan &p, const uint8_t *mask, int n_masks, int32_t *idx, int32_t *count,
                                    const float *x, const float *norm_g, void *ws, hipStream_t st);
