@@ -144,12 +144,17 @@ def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
 
 
 def _stream(stream) -> Optional[int]:
-    if stream is None:
-        stream = torch.cuda.current_stream()
+    if stream is None:  # the current stream's handle itself, without a Stream object around it
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
 def _need_cuda(name: str, t: torch.Tensor, dtypes, ndim: Optional[int] = None) -> None:
+    # Every tensor of every call comes through here (a stack's weights alone are 54): the usual case in one test, the
+    # reason only when it fails.
+    if (isinstance(t, torch.Tensor) and t.is_cuda and t.dtype in dtypes and t.is_contiguous()
+            and (ndim is None or t.dim() == ndim)):
+        return
     if not isinstance(t, torch.Tensor):
         raise TypeError(f"{name} must be a torch.Tensor")
     if t.device.type != "cuda":
@@ -182,10 +187,11 @@ def _weights(layer: Layer, B: Optional[int] = None) -> LayerWeights:
         raise ValueError("a layer is (w_gate, w_up, w_down, norm_g[, out_gate])")
     wg, wu, wd, g = layer[:4]
     gate = layer[4] if len(layer) == 5 else None
-    d_ff, d = wg.shape
+    full = wg.shape
+    d_ff, d = full
     for name, w in (("w_gate", wg), ("w_up", wu), ("w_down", wd)):
         _need_cuda(name, w, (wg.dtype,), 2)
-        if tuple(w.shape) != (d_ff, d):
+        if w.shape != full:
             raise ValueError(f"{name} has shape {tuple(w.shape)}, expected {(d_ff, d)} (neuron-major)")
     if g is not None:
         _need_cuda("norm_g", g, (torch.float32,), 1)
