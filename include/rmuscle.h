@@ -160,7 +160,7 @@ rm_status rm_sparse_ffn_stack(const rm_ffn_shape *s, const rm_ffn_layer_weights 
 /* rm_mask_compact followed by rm_sparse_ffn_layer, for a step that takes a freshly retrieved mask (section 4.1:
  * the reference's mask is compacted into its index list; section 5: one mask per layer and group).  The
  * compaction runs in the launch of the layer's first kernel (the two are independent), or ahead of the
- * one-launch layer kernel at d = 2048.  The result is rm_sparse_ffn_layer's on the written lists bit for bit,
+ * one-launch layer kernel at d = 2048 and of the float32 kernels.  The result is rm_sparse_ffn_layer's on the written lists bit for bit,
  * except for one sample at d = 1024, where rm_sparse_ffn_layer runs the one-launch layer kernel and this call
  * the prologue (with the compaction), gate/up and fused down kernels: there the two agree up to the order of
  * the float32 sums.
@@ -176,7 +176,7 @@ rm_status rm_masked_ffn_layer(const rm_ffn_shape *s, const rm_ffn_layer_weights 
                               int32_t max_count, void *ws, size_t ws_bytes, void *stream);
 
 /* rm_mask_compact of L * B masks followed by rm_sparse_ffn_stack (bit for bit), the compaction in the launch
- * of the stack's first kernel (ahead of the one-launch layer kernel at d = 2048).  mask: uint8 [L][B][d_ff];
+ * of the stack's first kernel (ahead of the one-launch layer kernel at d = 2048 and of the float32 kernels).  mask: uint8 [L][B][d_ff];
  * idx int32 [L][B][d_ff] and count int32 [L][B] out.  Otherwise as rm_masked_ffn_layer and
  * rm_sparse_ffn_stack. */
 rm_status rm_masked_ffn_stack(const rm_ffn_shape *s, const rm_ffn_layer_weights *w, int32_t L, int32_t B,
