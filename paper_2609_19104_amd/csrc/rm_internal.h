@@ -343,13 +343,15 @@ __device__ __forceinline__ float rm_gelu_tanh(float z) {
     return 0.5f * z * (1.0f + tanhf(0.7978845608028654f * (z + 0.044715f * z * z * z)));
 }
 
-// The same two for the bf16 kernels, whose h is rounded to bf16: both are z / (1 + e^-w), w = z for SiLU and, since
-// (1 + tanh u) / 2 = 1 / (1 + e^-2u), w = 2 u for GELU; with the hardware's exp2 and reciprocal (within an ulp or
-// two, against h's 8 bits) in place of expf, tanhf and a correctly rounded division.  The tiled gate/up kernel's tail
-// forms 10 h per thread: 16 samples x 18 layers of d = 1024, 1229 of 4096 neurons, 51 tokens 571.7 -> 559.4 us.
+// The same two for the bf16 kernels: both are z / (1 + e^-w), w = z for SiLU (rm_silu's bits) and, since
+// (1 + tanh u) / 2 = 1 / (1 + e^-2u), w = 2 u for GELU, which loses nothing where tanh u nears -1.  In float32 like
+// everything before h's rounding (an anchor keeps h as float32): largest relative error in units of 2^-24 for z in
+// [-80, 90] SiLU 2.9, GELU 2.4 for z > 0, 16 on [-3, -1] and 255 down to z = -10 (the rounding of w; the tanh form 216
+// and all of it).  The hardware's exp2 of -1.4427 w and its reciprocal take a few instructions less, but that product's
+// rounding costs SiLU 63 units at z = -80 and the reciprocal flushes to 0 from z = -88 on.
 __device__ __forceinline__ float rm_glu_act_bf16(int act, float z) {
     const float w = act == RM_ACT_GELU_TANH ? 1.5957691216057308f * (z + 0.044715f * z * z * z) : z;
-    return z * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * w));
+    return z / (1.0f + expf(-w));
 }
 
 // The gated linear unit's activation (act: an rm_act).
