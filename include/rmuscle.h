@@ -265,7 +265,8 @@ rm_status rm_context_workspace_size(const rm_ffn_shape *s, int32_t n_tok, int32_
  *             dense FFN reads every neuron, so both of its products take K-contiguous operands).
  *   x:        float32 [n_tok][d], the FFN input of every row (rounded to bf16 for the matrix cores).
  *   rows, count: the recomputed rows and their number (rm_context_select's outputs, read on the device);
- *             count is clamped to [0, max_rows] and rows outside [0, n_tok) to it.
+ *             count is clamped to [0, max_rows] and rows outside [0, n_tok) to it.  Of rows only the first count
+ *             entries are read.
  *   max_rows: host bound of count, in [1, n_tok]; sizes the launch and the workspace.
  *   y:        float32 [n_tok][d], in/out: the reference outputs on entry.
  *   ws, ws_bytes: at least rm_context_workspace_size(s, n_tok, max_rows) bytes, 16-byte aligned.

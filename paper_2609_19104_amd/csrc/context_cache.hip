@@ -166,15 +166,19 @@ __global__ __launch_bounds__(256) void pack_blocked_kernel(const uint16_t *__res
 // ------------------------------------------------------------------------------------------ gather
 
 // The listed rows of x as bf16 in the blocked layout [m_pad][d]; rows from the count up to m_pad are zero.  One workgroup
-// per row, two float4 per thread in flight (d = 2048: the whole row): 390 rows 7.2 -> 5.1 us against one wave per
-// row, whose loads went out 1 KB at a time.
+// per row, two float4 per thread in flight (d = 2048: the whole row): 390 rows 7.2 -> 5.0 us against one wave per
+// row, whose loads went out 1 KB at a time.  Of rows only the count's entries are read (a list may end there).
 __global__ __launch_bounds__(256) void gather_rows_kernel(const float *__restrict__ x, int d,
                                                           const int32_t *__restrict__ rows,
-                                                          const int32_t *__restrict__ count, int max_rows, int m_pad,
+                                                          const int32_t *__restrict__ count, int max_rows,
                                                           int n_tok, uint16_t *__restrict__ A) {
     const int i = blockIdx.x;
-    const int cnt = min(max(count[0], 0), max_rows);
-    const int r = min(max(rows[min(i, max_rows - 1)], 0), n_tok - 1);
+    if (i >= min(max(count[0], 0), max_rows)) {
+        for (int c = threadIdx.x * 4; c < d; c += 1024)
+            *reinterpret_cast<uint2 *>(A + blocked_offset(i, c, d)) = make_uint2(0u, 0u);
+        return;
+    }
+    const int r = min(max(rows[i], 0), n_tok - 1);
     const float *src = x + static_cast<size_t>(r) * d;
     for (int c0 = threadIdx.x * 4; c0 < d; c0 += 2048) {
         const int c1 = min(c0 + 1024, d - 4);
@@ -185,7 +189,6 @@ __global__ __launch_bounds__(256) void gather_rows_kernel(const float *__restric
             uint2 packed;
             packed.x = rm_f32_to_bf16_bits(v[k].x) | (rm_f32_to_bf16_bits(v[k].y) << 16);
             packed.y = rm_f32_to_bf16_bits(v[k].z) | (rm_f32_to_bf16_bits(v[k].w) << 16);
-            if (i >= cnt) packed = make_uint2(0u, 0u);
             if (c < d) *reinterpret_cast<uint2 *>(A + blocked_offset(i, c, d)) = packed;
         }
     }
@@ -507,7 +510,7 @@ hipError_t launch_context_ffn(const ContextPlan &p, const void *w_gate, const vo
                               void *ws, hipStream_t st) {
     char *base = static_cast<char *>(ws);
     hipLaunchKernelGGL(gather_rows_kernel, dim3(p.m_pad), dim3(256), 0, st, x, p.d, rows, count,
-                       p.max_rows, p.m_pad, p.n_tok, reinterpret_cast<uint16_t *>(base + p.off_a));
+                       p.max_rows, p.n_tok, reinterpret_cast<uint16_t *>(base + p.off_a));
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const auto *wg = static_cast<const uint16_t *>(w_gate);

@@ -141,6 +141,29 @@ def test_context_ffn_parity(d, d_ff, n_tok, v0, P, k, max_rows, act, packed):
     _check_update(w, w.x, w.y_ref, y, rows[:count], act)
 
 
+@pytest.mark.parametrize("packed", [False, True], ids=["row-major", "packed"])
+@pytest.mark.parametrize("n_tok,max_rows,count,d_ff", [(300, 300, 45, 256), (300, 260, 129, 2048), (40, 40, 1, 256)])
+def test_context_ffn_list_of_count_entries(n_tok, max_rows, count, d_ff, packed):
+    # The row list ends at the count, max_rows is a larger bound: what lies behind the list is another buffer's.  Here
+    # that is a guard in the same allocation whose entries, if taken for rows, would name the last row of all.
+    d = 128
+    w = wl.context_workload(n_tok=n_tok, v0=0, P=n_tok, d=d, d_ff=d_ff, seed=13)
+    rows = np.sort(np.random.default_rng(count).choice(n_tok - 1, count, replace=False)).astype(np.int32)
+    whole = _run_ffn(w, w.x, w.y_ref, rows, count, max_rows, "silu", packed=packed)
+    _check_update(w, w.x, w.y_ref, whole, rows, "silu")
+    xt, yt = dev_f32(w.x), dev_f32(w.y_ref)
+    guarded = torch.full((2 * n_tok,), n_tok - 1, dtype=torch.int32, device="cuda")
+    guarded[:count] = torch.from_numpy(rows).cuda()
+    ct = torch.tensor([count], dtype=torch.int32, device="cuda")
+    ws = rm.context_workspace(d, d_ff, n_tok, max_rows, act="silu")
+    mats = _bf16(w.layer.w_gate), _bf16(w.layer.w_up), _bf16(w.w_down_t)
+    if packed:
+        rm.rm_context_ffn_packed(xt, yt, rm.rm_context_pack(*mats, act="silu"), guarded[:count], ct, max_rows, ws, act="silu")
+    else:
+        rm.rm_context_ffn(xt, yt, *mats, guarded[:count], ct, max_rows, ws, act="silu")
+    assert np.array_equal(yt.cpu().numpy().view(np.uint32), whole.view(np.uint32))
+
+
 def _blocked_reference(m):
     """The documented blocked layout, written out with NumPy: 64 x 64 blocks, row tiles outermost, the blocks of a
     tile consecutive along K; in a block, row r's eight 16-byte pieces with piece p at position p ^ swz(r % 16),
