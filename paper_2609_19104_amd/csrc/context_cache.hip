@@ -28,6 +28,8 @@
 // 144 rows one of 160: the layer 106.9 -> 92.1 us.  Tiles of 256 rows keep 4 waves along the rows x 2 along the columns
 // (2 x 4: 91.4 -> 94.6 us for 492 rows at d_ff = 2176).
 // Workgroups that share a weight tile are numbered onto one XCD so that its L2 serves the re-reads.
+#include <algorithm>
+
 #include "rm_dma.h"
 #include "rm_select.h"
 
@@ -170,26 +172,29 @@ __global__ __launch_bounds__(256) void pack_blocked_kernel(const uint16_t *__res
 // row, whose loads went out 1 KB at a time.  Of rows only the count's entries are read (a list may end there).
 __global__ __launch_bounds__(256) void gather_rows_kernel(const float *__restrict__ x, int d,
                                                           const int32_t *__restrict__ rows,
-                                                          const int32_t *__restrict__ count, int max_rows,
+                                                          const int32_t *__restrict__ count, int max_rows, int m_pad,
                                                           int n_tok, uint16_t *__restrict__ A) {
-    const int i = blockIdx.x;
-    if (i >= min(max(count[0], 0), max_rows)) {
-        for (int c = threadIdx.x * 4; c < d; c += 1024)
-            *reinterpret_cast<uint2 *>(A + blocked_offset(i, c, d)) = make_uint2(0u, 0u);
-        return;
-    }
-    const int r = min(max(rows[i], 0), n_tok - 1);
-    const float *src = x + static_cast<size_t>(r) * d;
-    for (int c0 = threadIdx.x * 4; c0 < d; c0 += 2048) {
-        const int c1 = min(c0 + 1024, d - 4);
-        const float4 v[2] = {*reinterpret_cast<const float4 *>(src + c0), *reinterpret_cast<const float4 *>(src + c1)};
+    const int cnt = min(max(count[0], 0), max_rows);
+    for (int i = blockIdx.x; i < m_pad; i += gridDim.x) {
+        if (i >= cnt) {
+            for (int c = threadIdx.x * 4; c < d; c += 1024)
+                *reinterpret_cast<uint2 *>(A + blocked_offset(i, c, d)) = make_uint2(0u, 0u);
+            continue;
+        }
+        const int r = min(max(rows[i], 0), n_tok - 1);
+        const float *src = x + static_cast<size_t>(r) * d;
+        for (int c0 = threadIdx.x * 4; c0 < d; c0 += 2048) {
+            const int c1 = min(c0 + 1024, d - 4);
+            const float4 v[2] = {*reinterpret_cast<const float4 *>(src + c0),
+                                 *reinterpret_cast<const float4 *>(src + c1)};
 #pragma unroll
-        for (int k = 0; k < 2; ++k) {
-            const int c = c0 + 1024 * k;
-            uint2 packed;
-            packed.x = rm_f32_to_bf16_bits(v[k].x) | (rm_f32_to_bf16_bits(v[k].y) << 16);
-            packed.y = rm_f32_to_bf16_bits(v[k].z) | (rm_f32_to_bf16_bits(v[k].w) << 16);
-            if (c < d) *reinterpret_cast<uint2 *>(A + blocked_offset(i, c, d)) = packed;
+            for (int k = 0; k < 2; ++k) {
+                const int c = c0 + 1024 * k;
+                uint2 packed;
+                packed.x = rm_f32_to_bf16_bits(v[k].x) | (rm_f32_to_bf16_bits(v[k].y) << 16);
+                packed.y = rm_f32_to_bf16_bits(v[k].z) | (rm_f32_to_bf16_bits(v[k].w) << 16);
+                if (c < d) *reinterpret_cast<uint2 *>(A + blocked_offset(i, c, d)) = packed;
+            }
         }
     }
 }
@@ -509,8 +514,9 @@ hipError_t launch_context_ffn(const ContextPlan &p, const void *w_gate, const vo
                               bool blocked, const float *x, const int32_t *rows, const int32_t *count, float *y,
                               void *ws, hipStream_t st) {
     char *base = static_cast<char *>(ws);
-    hipLaunchKernelGGL(gather_rows_kernel, dim3(p.m_pad), dim3(256), 0, st, x, p.d, rows, count,
-                       p.max_rows, p.n_tok, reinterpret_cast<uint16_t *>(base + p.off_a));
+    const int groups = std::min(p.m_pad, 1 << 20);  // (2^32 threads or more wrap without an error)
+    hipLaunchKernelGGL(gather_rows_kernel, dim3(groups), dim3(256), 0, st, x, p.d, rows, count,
+                       p.max_rows, p.m_pad, p.n_tok, reinterpret_cast<uint16_t *>(base + p.off_a));
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const auto *wg = static_cast<const uint16_t *>(w_gate);
