@@ -86,6 +86,12 @@ hipError_t launch_identity_prologue(const Plan &p, const float *x, const float *
     const int n_lists = static_cast<int>(std::min<size_t>((n + 255) / 256, 1024));
     const int nblk = (p.d + kRowBlock - 1) / kRowBlock;
     const int units = p.B * p.T * nblk;
+    // A grid of 2^32 threads or more wraps without an error: where the lists' workgroups do not fit beside the
+    // prologue's, two launches.
+    if ((n_lists + (units + 3LL) / 4) * 256 > 0xffffffffLL) {
+        const hipError_t e = launch_identity_lists(p, ws, st);
+        return e != hipSuccess ? e : launch_prologue(p, x, norm_g, ws, st);
+    }
     hipLaunchKernelGGL(identity_prologue_kernel, dim3(n_lists + (units + 3) / 4), dim3(256), 0, st, idx, count, p.d_ff,
                        p.B, n_lists, x, norm_g, p.d, nblk, units, reinterpret_cast<uint16_t *>(base + p.off_xn),
                        reinterpret_cast<float *>(base + p.off_ssq));

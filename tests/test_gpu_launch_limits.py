@@ -43,3 +43,16 @@ def test_context_ffn_with_more_rows_than_workgroups_of_a_launch():
     _close(y[listed], _glu(x[listed], wg, wu) @ wd.double().t())
     y[listed] = 0.0
     assert not bool(y.any())
+
+
+def test_dense_layer_with_as_many_rows_as_the_prologue_takes():
+    # The prologue's 64 threads per token just fit a launch; beside the identity lists' workgroups they would not.
+    T, d, d_ff = 67108860, 32, 32
+    if torch.cuda.mem_get_info()[0] < 48e9:
+        pytest.skip("needs 48 GB")
+    wg, wu, wd = _weights(3, (d_ff, d), (d_ff, d), (d_ff, d))
+    x = torch.randn(1, T, d, device="cuda", generator=torch.Generator(device="cuda").manual_seed(4))
+    at = torch.cat([torch.arange(100), torch.arange(T // 2, T // 2 + 100), torch.arange(T - 100, T)]).cuda()
+    xs = x[0, at].clone()
+    rm.rm_dense_ffn_ref(x, x, (wg, wu, wd, None), rm.workspace(d, d_ff, rm.RM_BF16, 1, T, d_ff))
+    _close(x[0, at] - xs, _glu(xs, wg, wu) @ wd.double())
