@@ -20,6 +20,12 @@
 //   PD chunks in flight; their tiles are added in wave order through LDS.  One slice: the kernel adds the residual
 //   itself (kFused); several: float32 partials that the epilogue kernel adds in slice order.
 //
+// Rounding.  One chain of sums per wave over all its columns (d / 8) or slots (list / 8) loses more than the 8-lane dot
+// products and short slices that these kernels replaced.  So gate/up starts at zero for every 8 columns and the down
+// kernel for every chunk of 16 slots, and those sums are added up: error of an FFN output against 64 bits (2-norm, units of
+// 2^-24; before the matrix cores, one chain, now) 6.2, 6.8, 3.9 at d = 1024 and 1229 neurons, 6.4, 8.8, 4.1 at 4096, 8.5,
+// 10.6, 4.6 at d = 2048 and 5000, 3.0, 3.5, 2.8 at d = 256 and 256; the time stays (18.4 -> 18.3 us for the layer below).
+//
 // What bounds them.  At T = 51 a listed neuron is 12 KB of weights and 0.31 MFLOP at d = 1024: 26 FLOP per byte
 // against a ridge of 28 (145 TFLOP/s measured from these instructions over a 5.2 TB/s copy), so the matrix cores have
 // to be used: a vector-ALU product of 8 tokens at a time, one wave per 8 neurons, read every weight 7 times.  One
@@ -175,11 +181,13 @@ __global__ __launch_bounds__(kThreads, 4) void gateup_f32_kernel(GuArgs a) {
             for (int tt = 0; tt < NT; ++tt)
                 bx[tt] = *reinterpret_cast<const rm_f32x4 *>(region + tt * 16 * kPitch + frag);
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
+            for (int j = 0; j < 4; j += 2)  // 8 columns' own sums, see above
 #pragma unroll
                 for (int tt = 0; tt < NT; ++tt)
 #pragma unroll
-                    for (int g = 0; g < NG; ++g) acc[g][tt] = mfma_f32(aw[g][j], bx[tt][j], acc[g][tt]);
+                    for (int g = 0; g < NG; ++g)
+                        acc[g][tt] += mfma_f32(aw[g][j + 1], bx[tt][j + 1],
+                                               mfma_f32(aw[g][j], bx[tt][j], rm_f32x4{0.f, 0.f, 0.f, 0.f}));
         }
     }
     // The wave's tiles and its share of the tokens' squares.
@@ -355,11 +363,18 @@ __global__ __launch_bounds__(kThreads, 4) void down_f32_kernel(DnArgs a) {
                     }
                 }
 #pragma unroll
-                for (int j = 0; j < 4; ++j)
+                for (int q = 0; q < CW; ++q) {
+                    rm_f32x4 chunk[NT];  // the chunk's own sums, see above
 #pragma unroll
-                    for (int tt = 0; tt < NT; ++tt)
+                    for (int tt = 0; tt < NT; ++tt) chunk[tt] = rm_f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                        for (int q = 0; q < CW; ++q) acc[tt][q] = mfma_f32(hv[p][tt][j], wv[p][j][q], acc[tt][q]);
+                    for (int j = 0; j < 4; ++j)
+#pragma unroll
+                        for (int tt = 0; tt < NT; ++tt) chunk[tt] = mfma_f32(hv[p][tt][j], wv[p][j][q], chunk[tt]);
+#pragma unroll
+                    for (int tt = 0; tt < NT; ++tt) acc[tt][q] += chunk[tt];
+                    if constexpr (NT * CW > 4) __builtin_amdgcn_sched_barrier(0);  // one column's sums at a time
+                }
                 load_h(p, k0 + p + PD, c0);
                 load_w(p, k0 + p + PD);
             }

@@ -14,6 +14,7 @@ pytestmark = pytest.mark.gpu
 if not torch.cuda.is_available():
     pytest.skip("needs a GPU", allow_module_level=True)
 
+import paper_2609_19104_amd as rm  # noqa: E402
 from gpu_helpers import TOL_F32, compact, dev_weights, errors, run_layer  # noqa: E402
 
 # d, d_ff, T, counts, max_count, norm
@@ -51,3 +52,32 @@ def test_f32_layer_edges(d, d_ff, T, counts, max_count, norm):
         ref = oracle.masked_ffn(x[b], wg, wu, wd, masks[b].astype(np.float64), g)
         ey, ed = errors(y[b], ref, x[b])
         assert ey <= TOL_F32 and ed <= TOL_F32, f"sample {b} count {c}: rel err y {ey:.3e}, delta {ed:.3e}"
+
+
+# The bars are the errors of plain 8-lane dot products and short slices, each rounded once per term, on these inputs.  One
+# chain of sums per wave over d / 8 columns and a list's eighth of the slots is above them (h 2.9, 5.5, 5.6; FFN 3.5, 6.8,
+# 8.8), chains of 8 columns and 16 slots that are then added up are below (2.3, 3.4, 3.4; 2.8, 3.9, 4.1).
+@pytest.mark.parametrize("d,d_ff,T,norm,bar_h,bar_f", [(256, 256, 8, False, 2.54, 3.02), (1024, 1229, 51, True, 5.41, 6.16),
+                                                       (1024, 4096, 51, True, 5.46, 6.43)])
+def test_f32_rounding_error(d, d_ff, T, norm, bar_h, bar_f):
+    # Through an anchor step, which keeps h and the FFN output without the residual.  2-norm error in units of 2^-24.
+    g = torch.Generator(device="cuda").manual_seed(d + d_ff + T + 1)
+    draw = lambda *s: torch.randn(*s, generator=g, device="cuda")  # noqa: E731
+    w = [draw(d_ff, d) * 0.02 for _ in range(3)]
+    gain = 1 + 0.1 * draw(d) if norm else None
+    x = draw(1, T, d)
+    idx = torch.arange(d_ff, dtype=torch.int32, device="cuda").view(1, 1, d_ff)
+    cnt = torch.full((1, 1), d_ff, dtype=torch.int32, device="cuda")
+    ya, ha = torch.empty(1, 1, T, d, device="cuda"), torch.empty(1, 1, d_ff, T, device="cuda")
+    rm.rm_anchor_ffn_stack(x, torch.empty_like(x), [(*w, gain)], idx, cnt, d_ff, ya, ha,
+                           rm.workspace(d, d_ff, rm.RM_F32, 1, T, d_ff))
+    xd = x[0].double()
+    if norm:
+        xd = xd / torch.sqrt((xd * xd).mean(-1, keepdim=True) + 1e-6) * gain.double()
+    a, b = xd @ w[0].double().t(), xd @ w[1].double().t()
+    h = a * torch.sigmoid(a) * b
+    f = h @ w[2].double()
+    units = lambda got, ref: float((got.double() - ref).norm() / ref.norm()) * 2 ** 24  # noqa: E731
+    eh, ef = units(ha[0, 0].t(), h), units(ya[0, 0], f)
+    print(f"rounding error: h {eh:.2f}, FFN {ef:.2f} units of 2^-24")
+    assert eh <= bar_h and ef <= bar_f
