@@ -521,7 +521,7 @@ __global__ __launch_bounds__(kGuThreads) void gateup_staged_unrolled_kernel(GuAr
 
 // ------------------------------------------------------------------------------------------ gate / up, pipelined
 
-// For long lists (T <= 64, d = 256 NCH with NCH in {1, 2, 4, 8}).  NG groups of 8 neurons per workgroup as
+// For long lists (T <= 64, d = 256 NCH with NCH in {1, 2, 4, 8}; the plan says which).  NG groups of 8 neurons per workgroup as
 // in the staged kernel; column chunk c of the FFN input (64 token rows x 256 columns) is shared by the groups
 // through LDS.  Every wave loads its share of chunk c's input (whole 512-byte rows) together with its weights
 // for chunk c, P chunks ahead, input first.  A wave's memory counter completes in issue order, so waiting for
@@ -535,7 +535,7 @@ __global__ __launch_bounds__(kGuThreads, (NG == 2 || kTwoPerCU) ? 4 : 2) void ga
     constexpr int NT = 4;
     constexpr int DS = kGuWaves / NG;  // waves per neuron group (d split within a chunk)
     constexpr int SPW = kChunkSteps / DS;  // K steps per wave and chunk
-    constexpr int P0 = kTwoPerCU ? (NG == 2 ? 3 : 2) : (NG == 8 ? 3 : (NG == 4 ? 4 : 3));  // chunks in flight
+    constexpr int P0 = NG == 4 ? 4 : (NG == 8 && kTwoPerCU ? 2 : 3);  // chunks in flight
     constexpr int P = P0 < NCH ? P0 : NCH;
     const int q = xcd_logical(blockIdx.x, gridDim.x);  // = block * B + sample
     const int b = q % a.B;
@@ -1790,9 +1790,7 @@ hipError_t launch_gateup_nt(const rm::Plan &p, const GuArgs &a, hipStream_t st) 
         const bool two = static_cast<long long>(p.gate_blocks) * p.B > 256;  // more workgroups than compute units
         switch (p.gate_groups) {
             case 2: RM_PIPE(2, true) break;
-            case 4:
-                if (two) RM_PIPE(4, true) else RM_PIPE(4, false)
-                break;
+            case 4: RM_PIPE(4, false) break;
             default:
                 if (two) RM_PIPE(8, true) else RM_PIPE(8, false)
                 break;

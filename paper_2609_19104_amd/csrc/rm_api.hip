@@ -330,12 +330,13 @@ rm_status make_plan(const rm_ffn_shape *s, int B, int T, int max_count, Plan *p,
     constexpr int kTargetDownGroups = RM_DOWN_TARGET;
     if (s->wdtype == RM_BF16) {
         q.tpad = ceil_div(T, kBfTokBlock) * kBfTokBlock;
-        // Gate/up workgroups of 8 * NG neurons.  Measured at d = 2048 (one sample) and d = 1024 (16 samples):
-        // one round of workgroups that fills most compute units is best (the widest NG with 150 .. 256
-        // workgroups); a grid just past the compute units (256 .. 384 workgroups) is the worst case, since the
-        // compute units that get a second workgroup set the time, so a grid there takes the next narrower NG
-        // (more, lighter workgroups); otherwise the widest NG that still gives every compute unit one
-        // workgroup, or one group of 8 per workgroup (the direct kernel, when d allows) for short lists.
+        // Gate/up workgroups of 8 * NG neurons (it also sets kcap, and with it the workspace, of the calls that the
+        // tiled kernel below takes).  Measured at d = 2048 with one sample: one round of workgroups that fills most
+        // compute units is best (the widest NG with 150 .. 256 workgroups); a grid just past the compute units
+        // (256 .. 384 workgroups) is the worst case, since the compute units that get a second workgroup set the time,
+        // so a grid there takes the next narrower NG (more, lighter workgroups); otherwise the widest NG that still
+        // gives every compute unit one workgroup, or one group of 8 per workgroup (the direct kernel, when d allows)
+        // for short lists.
         const int k32 = ceil_div(kmax, kBfChunk) * kBfChunk;
         const bool direct_ok = s->d == 256 || s->d == 512 || s->d == 1024 || s->d == 2048;
         // One sample with more groups of 8 slots than compute units (up to 3 per unit): the spread kernel, one
@@ -369,13 +370,21 @@ rm_status make_plan(const rm_ffn_shape *s, int B, int T, int max_count, Plan *p,
         // workgroups share a staged input between up to 12 groups.  Below that its longer workgroups leave too little
         // in flight (calls, other kernels -> tiled: 464 groups 517.5 -> 539.5 us, 616 23.3 -> 24.0, 720 146 -> 155,
         // 924 31.7 -> 32.6; 1048 210 -> 183, 1100 40.8 -> 28.4, 1390 27.7 -> 23.0, 2464 653 -> 560, 4376 118 -> 79).
-        // One sample at d = 2048 keeps the pipelined kernel (16384 neurons: both read at the memory's rate, 58.5 against
-        // 59.1 us).  Groups per workgroup: the fewest rounds over the chip, a workgroup counted as 16 groups' time plus
-        // its groups'.
+        // One sample keeps the pipelined kernel where its workgroups fill 15/16 of its rounds (of one workgroup per
+        // compute unit, or of two past 256).  Calls, pipelined | tiled us: at d = 2048 8192 neurons (256 workgroups)
+        // 35.9 | 36.5, 8704 (544) 49.4 | 43.4, 12288 (192) 54.3 | 48.2, 14336 (224) 55.7 | 52.8, 15360 (240) 55.4 | 56.2,
+        // 16384 (256) 59.2 | 60.4, 24576 (768) 82.9 | 79.3, 32768 (512) 103.3 | 109.1; at d = 256 8192 20.5 | 21.4, 16384
+        // 23.0 | 24.2.  Rows of 2 or 4 chunks (of 256 columns) in one round of 8 groups
+        // measure the other way, 28.6 | 27.2 at d = 512 and 36.3 | 35.1 at 1024 (16384; in 4 groups, 8192: 21.2 | 22.0 and
+        // 25.7 | 25.8; two workgroups per compute unit, 32768: 39.2 | 42.4 and 58.7 | 62.2), and go to the tiled kernel.
+        // Groups per workgroup: the fewest rounds over the chip, a workgroup counted as 16 groups' time plus its groups'.
         const int tblocks = ceil_div(T, kBfTokBlock);
         const long long groups = static_cast<long long>(n8) * tblocks * B;
-        if (groups >= 4 * kCUs && groups / 12 < (1 << 22) /* grid limit */ &&
-            !(B == 1 && T <= kBfTokBlock && s->d == 2048)) {
+        const int slots = q.gate_blocks > kCUs ? 2 * kCUs : kCUs;  // pipelined workgroups per round (one sample)
+        const bool pipe = B == 1 && T <= kBfTokBlock && direct_ok &&
+                          16LL * q.gate_blocks >= 15LL * slots * ceil_div(q.gate_blocks, slots) &&
+                          !(q.gate_groups == 8 && slots == kCUs && s->d > 256 && s->d <= 1024);
+        if (groups >= 4 * kCUs && groups / 12 < (1 << 22) /* grid limit */ && !pipe) {
             q.gate_tblocks = tblocks;
             q.gate_nt = ceil_div(ceil_div(T, tblocks), 16);
             long long best = -1;

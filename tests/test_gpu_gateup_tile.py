@@ -23,6 +23,13 @@ CASES = [
     (2080, 800, 20, 12, 700, "random"), # more than 64 norm partials per row
     (64, 2600, 51, 8, 2561, "none"),    # one stage; lists of 81 chunks, 12 groups per workgroup
     (320, 9000, 5, 1, 8201, "ones"),    # one sample
+    # One sample at the pipelined kernel's widths, on both sides of the rule that chooses between the two.
+    (256, 8300, 5, 1, 8192, "random"),    # pipelined, 256 workgroups of 4 groups
+    (256, 8300, 5, 1, 8193, "random"),    # tiled (514 workgroups of 2)
+    (256, 15500, 3, 1, 15297, "none"),    # pipelined, 240 workgroups of 8
+    (256, 15500, 3, 1, 15296, "none"),    # tiled (239)
+    (512, 16400, 3, 1, 16384, "random"),  # tiled: one round of 8 groups over 2 chunks
+    (512, 31000, 2, 1, 30657, "none"),    # pipelined, 480 workgroups of 8, two per compute unit
 ]
 
 
