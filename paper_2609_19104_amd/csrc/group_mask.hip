@@ -207,7 +207,7 @@ __global__ __launch_bounds__(kThreads) void step_select_kernel(const float *__re
 }
 
 // The layer's mask: the K members of the union (mask bytes set by step_select_kernel) with the largest score
-// summed over the steps in step order.  The union holds at least K neurons.
+// summed over the steps in step order.  The union holds at least K neurons (every step's K), mostly fewer than d_ff.
 // Bound by latency: one workgroup per layer, whose loads are round trips.  18 layers of 4096 neurons, 5 steps: 18.6 us
 // with one step's scores in flight, each thread's 16 neurons consecutive (every load instruction touching 64 lines)
 // and digits from bit 31 on; 7.7 us with four steps in flight, the neurons dealt in turn, and rm_select.h's digits

@@ -65,14 +65,15 @@ __device__ __forceinline__ int block_excl_scan(int v, SelLds<kThreads> &l) {
 
 // Items are dealt to the threads in turn: item i * kThreads + tid is the thread's i-th, so that a wave's loads and
 // stores of one i are consecutive.  Selection bits (bit i: the thread's i-th item) of the k largest keys among the
-// valid ones (bit i of `valid`; n_valid of them in the workgroup or more), ties to the lower item index.  0 <= k; every
-// thread of the workgroup calls it.
+// valid ones (bit i of `valid`), ties to the lower item index; all valid ones where they are k or fewer.  n_most: at
+// least the number of valid items in the workgroup (k >= n_most saves the passes).  0 <= k; every thread of the
+// workgroup calls it.
 template <int kThreads>
-__device__ inline uint32_t select_top_k(const uint32_t (&key)[kSelPerThread], uint32_t valid, int k, int n_valid,
+__device__ inline uint32_t select_top_k(const uint32_t (&key)[kSelPerThread], uint32_t valid, int k, int n_most,
                                         SelLds<kThreads> &l) {
     static_assert(kThreads >= 256, "wave 0 finds the digit while at least three other waves clear histograms");
     if (k <= 0) return 0u;
-    if (k >= n_valid) return valid;
+    if (k >= n_most) return valid;
     constexpr int kWaves = kThreads / 64;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     uint32_t lo = 0xffffffffu, hi = 0u;
@@ -91,6 +92,7 @@ __device__ inline uint32_t select_top_k(const uint32_t (&key)[kSelPerThread], ui
         l.wave_hi[wave] = hi;
     }
     for (int b = lane; b < 256; b += 64) l.whist[0][wave][b] = 0u;
+    if (tid == 0) l.digit = l.need = l.in_digit = 0;  // stays so if fewer than k are valid: every digit from 0 on is taken
     __syncthreads();
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) {
