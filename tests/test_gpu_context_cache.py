@@ -128,10 +128,16 @@ FFN_CASES = [
 TILE_CASES = [(d, d_ff, n, 0, n, n, n, "silu") for d, d_ff, n in
               [(128, 256, 128), (128, 2048, 129), (192, 128, 161), (192, 2048, 193), (128, 256, 225), (128, 2048, 256),
                (128, 128, 257), (192, 2048, 390), (128, 256, 449), (64, 128, 513), (128, 2048, 768)]]
+# Counts below max_rows: tiles of 128 to 256 rows (max_rows 128 to 512 in one and two tiles, 513 in three of 192), the last
+# tile in use full, with one row, and the tiles behind it wholly past the count.
+COUNT_CASES = [(128, d_ff, max_rows, 0, max_rows, count, max_rows, "silu") for d_ff, max_rows, count in
+               [(256, 128, 1), (2048, 128, 127), (256, 320, 160), (2048, 320, 161), (256, 320, 319), (256, 380, 192),
+                (2048, 380, 193), (256, 448, 224), (2048, 448, 225), (256, 512, 256), (2048, 512, 257), (256, 512, 9),
+                (256, 513, 192), (2048, 513, 193), (256, 513, 384), (2048, 513, 385)]]
 
 
 @pytest.mark.parametrize("packed", [False, True], ids=["row-major", "packed"])
-@pytest.mark.parametrize("d,d_ff,n_tok,v0,P,k,max_rows,act", FFN_CASES + TILE_CASES)
+@pytest.mark.parametrize("d,d_ff,n_tok,v0,P,k,max_rows,act", FFN_CASES + TILE_CASES + COUNT_CASES)
 def test_context_ffn_parity(d, d_ff, n_tok, v0, P, k, max_rows, act, packed):
     w = wl.context_workload(n_tok=n_tok, v0=v0, P=P, d=d, d_ff=d_ff, seed=7 + d)
     drift = cc.drift(w.x[v0:v0 + P], w.x_ref[v0:v0 + P])

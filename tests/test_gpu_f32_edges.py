@@ -28,8 +28,8 @@ CASES = [
     (2048, 2304, 33, [2100], 2100, "none"),        # one slice longer than the 2048 staged indices
     (1024, 4096, 51, [1229], 1229, "random"),      # 16 neurons per gate/up workgroup
     (512, 700, 40, [300, 299, 1, 64, 65, 500, 0, 128], 500, "ones"),  # 64-column x 32-token down tiles
-    (544, 700, 65, [201, 333], 340, "random"),     # three token blocks; a column tile past d
-    (1056, 520, 64, [500, 513, 7, 130], 520, "none"),  # the same with 64-column tiles
+    (544, 700, 65, [201, 333], 340, "random"),     # three token blocks
+    (1056, 520, 64, [500, 513, 7, 130], 520, "none"),  # 64-column tiles, the last one half past d
 ]
 
 
@@ -81,3 +81,45 @@ def test_f32_rounding_error(d, d_ff, T, norm, bar_h, bar_f):
     eh, ef = units(ha[0, 0].t(), h), units(ya[0, 0], f)
     print(f"rounding error: h {eh:.2f}, FFN {ef:.2f} units of 2^-24")
     assert eh <= bar_h and ef <= bar_f
+
+
+# d, d_ff, L, B, T, longest list.  The down kernel's forms: 64 columns x 32 tokens with the last column tile half past d; the
+# list in slices with the epilogue (two for the lists, three for the dense anchor); 32 x 16 in one slice.
+EQ4_CASES = [(544, 300, 2, 5, 70, 200), (64, 2300, 3, 1, 3, 1500), (96, 150, 2, 2, 17, 65)]
+
+
+@pytest.mark.parametrize("d,d_ff,L,B,T,k", EQ4_CASES)
+def test_f32_eq4_gates_and_stacks(d, d_ff, L, B, T, k):
+    # Anchor, delta and plain stacks with output gates, y in place of x as well; a delta step at the anchor's own input is
+    # the anchor bit for bit.
+    layers = [wl.make_layer(94, l, d, d_ff, "f32", norm="random") for l in range(L)]
+    r = np.random.default_rng(95)
+    gates = [(1.0 + 0.3 * r.standard_normal((B, d))).astype(np.float32) for _ in range(L)]
+    dev = [dev_weights(l) + (torch.from_numpy(g).cuda(),) for l, g in zip(layers, gates)]
+    xa = wl.make_x(94, (B, T, d), d_ff, T)
+    xt = (xa + 0.05 * r.standard_normal(xa.shape)).astype(np.float32)
+    masks = np.stack([wl.ragged_masks(94, d_ff, [k - 7 * b for b in range(B)], l) for l in range(L)])
+    idx, cnt = compact(masks.reshape(L * B, d_ff))
+    to = lambda a: torch.from_numpy(a).cuda()  # noqa: E731
+    ya, ha = torch.empty(L, B, T, d, device="cuda"), torch.empty(L, B, k, T, device="cuda")
+    ws_d = rm.workspace(d, d_ff, rm.RM_F32, B, T, d_ff)
+    ws = rm.workspace(d, d_ff, rm.RM_F32, B, T, k)
+    y_a = to(xa)
+    rm.rm_anchor_ffn_stack(y_a, y_a, dev, idx, cnt, k, ya, ha, ws_d, act="gelu_tanh")
+    y_t, y_same, y_s, y_in = to(xt), torch.empty_like(y_a), torch.empty_like(y_a), to(xt)
+    rm.rm_delta_ffn_stack(y_t, y_t, dev, idx, cnt, k, ya, ha, ws, act="gelu_tanh")
+    rm.rm_delta_ffn_stack(to(xa), y_same, dev, idx, cnt, k, ya, ha, ws, act="gelu_tanh")
+    rm.rm_sparse_ffn_stack(to(xt), y_s, dev, idx, cnt, k, ws, act="gelu_tanh")
+    rm.rm_sparse_ffn_stack(y_in, y_in, dev, idx, cnt, k, ws, act="gelu_tanh")
+    assert torch.equal(y_same, y_a) and torch.equal(y_in, y_s)
+    lay = [l.f64() for l in layers]
+    for b in range(B):
+        g = [q[b] for q in gates]
+        m = [masks[l, b].astype(np.float64) for l in range(L)]
+        ra, rya, rha = oracle.anchor_stack(xa[b], lay, act="gelu_tanh", gates=g)
+        rt = oracle.delta_stack(xt[b], lay, m, rya, rha, act="gelu_tanh", gates=g)
+        rs = oracle.ffn_stack(xt[b], lay, m, act="gelu_tanh", gates=g)
+        assert oracle.rel_err(ya[:, b].cpu().numpy().astype(np.float64), rya) <= TOL_F32
+        for name, got, ref, x in (("anchor", y_a, ra, xa), ("delta", y_t, rt, xt), ("stack", y_s, rs, xt)):
+            ey, ed = errors(got[b].cpu().numpy(), ref, x[b])
+            assert ey <= TOL_F32 and ed <= TOL_F32, f"{name} sample {b}: rel err y {ey:.3e}, delta {ed:.3e}"

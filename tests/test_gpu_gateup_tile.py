@@ -42,12 +42,19 @@ def test_tiled_gateup_edges(d, d_ff, T, B, k, norm):
     idx, cnt = compact(masks)
     y = run_layer(dev_weights(layer), x, idx, cnt, k)
     wg, wu, wd, g = layer.f64()
-    for b, c in enumerate(counts[:16]):
+    refs = np.stack([oracle.masked_ffn(x[b], wg, wu, wd, masks[b].astype(np.float64), g) for b in range(B)])
+    for b, c in enumerate(counts):
         if c == 0:
             assert np.array_equal(y[b].view(np.uint32), x[b].view(np.uint32))
-            continue
-        ey, ed = errors(y[b], oracle.masked_ffn(x[b], wg, wu, wd, masks[b].astype(np.float64), g), x[b])
-        assert ey <= TOL_BF16 and ed <= TOL_BF16, f"sample {b} count {c}: rel err y {ey:.3e}, delta {ed:.3e}"
+        elif b < 16:
+            ey, ed = errors(y[b], refs[b], x[b])
+            assert ey <= TOL_BF16 and ed <= TOL_BF16, f"sample {b} count {c}: rel err y {ey:.3e}, delta {ed:.3e}"
+    # Every sample, those of one count together: the input's rounding is relative to the products, not to their sum, so one
+    # neuron whose up sum cancels (-0.009 out of products of 0.1 in sample 66 of the first case) is 5 % off by itself.
+    for c in sorted(set(counts) - {0}):
+        same = [b for b in range(B) if counts[b] == c]
+        ey, ed = errors(y[same], refs[same], x[same])
+        assert ey <= TOL_BF16 and ed <= TOL_BF16, f"samples of count {c}: rel err y {ey:.3e}, delta {ed:.3e}"
     assert np.isfinite(y).all()
 
 
