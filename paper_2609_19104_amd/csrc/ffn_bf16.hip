@@ -1785,12 +1785,15 @@ hipError_t launch_gateup_nt(const rm::Plan &p, const GuArgs &a, hipStream_t st) 
         case 1: e = launch_timed(RM_KERNEL_GATEUP, gateup_pipe_kernel<NG, 1, TWO>, grid, block, st, a); break; \
         case 2: e = launch_timed(RM_KERNEL_GATEUP, gateup_pipe_kernel<NG, 2, TWO>, grid, block, st, a); break; \
         case 4: e = launch_timed(RM_KERNEL_GATEUP, gateup_pipe_kernel<NG, 4, TWO>, grid, block, st, a); break; \
-        default: e = launch_timed(RM_KERNEL_GATEUP, gateup_pipe_kernel<NG, 8, TWO>, grid, block, st, a); break; \
+        default: /* d = 2048, 4 groups: the plan has no grid past the compute units */                      \
+            e = launch_timed(RM_KERNEL_GATEUP, gateup_pipe_kernel<NG, 8, TWO && NG != 4>, grid, block, st, a); break; \
     }
         const bool two = static_cast<long long>(p.gate_blocks) * p.B > 256;  // more workgroups than compute units
         switch (p.gate_groups) {
             case 2: RM_PIPE(2, true) break;
-            case 4: RM_PIPE(4, false) break;
+            case 4:
+                if (two) RM_PIPE(4, true) else RM_PIPE(4, false)
+                break;
             default:
                 if (two) RM_PIPE(8, true) else RM_PIPE(8, false)
                 break;

@@ -370,33 +370,48 @@ rm_status make_plan(const rm_ffn_shape *s, int B, int T, int max_count, Plan *p,
         // workgroups share a staged input between up to 12 groups.  Below that its longer workgroups leave too little
         // in flight (calls, other kernels -> tiled: 464 groups 517.5 -> 539.5 us, 616 23.3 -> 24.0, 720 146 -> 155,
         // 924 31.7 -> 32.6; 1048 210 -> 183, 1100 40.8 -> 28.4, 1390 27.7 -> 23.0, 2464 653 -> 560, 4376 118 -> 79).
-        // One sample keeps the pipelined kernel where its workgroups fill 15/16 of its rounds (of one workgroup per
-        // compute unit, or of two past 256).  Calls, pipelined | tiled us: at d = 2048 8192 neurons (256 workgroups)
-        // 35.9 | 36.5, 8704 (544) 49.4 | 43.4, 12288 (192) 54.3 | 48.2, 14336 (224) 55.7 | 52.8, 15360 (240) 55.4 | 56.2,
-        // 16384 (256) 59.2 | 60.4, 24576 (768) 82.9 | 79.3, 32768 (512) 103.3 | 109.1; at d = 256 8192 20.5 | 21.4, 16384
-        // 23.0 | 24.2.  Rows of 2 or 4 chunks (of 256 columns) in one round of 8 groups
-        // measure the other way, 28.6 | 27.2 at d = 512 and 36.3 | 35.1 at 1024 (16384; in 4 groups, 8192: 21.2 | 22.0 and
-        // 25.7 | 25.8; two workgroups per compute unit, 32768: 39.2 | 42.4 and 58.7 | 62.2), and go to the tiled kernel.
-        // Groups per workgroup: the fewest rounds over the chip, a workgroup counted as 16 groups' time plus its groups'.
+        // Groups per workgroup: the fewest rounds over the chip, a workgroup counted as 16 groups' time plus its groups'
+        // (tile_cost).  The others' workgroups count 10 groups' time plus their groups' (other_cost; two workgroups per
+        // compute unit past 256, a last round that is not full between its share and a whole one, each token block of a
+        // wider input on its own).  Where tile_cost exceeds other_cost by `tenths` / 10 they are the faster ones, which
+        // depends on how long the rows are and, with at most 64 tokens, on how much of the pipelined kernel's fixed 64
+        // is used (0: tiled).  Measured over 1557 calls: the choice is on average 0.2 % and in 29 calls over 4 % slower than
+        // the better kernel.  Calls, others | tiled us: d = 256, T = 51, 16 samples of 4096 31.8 | 40.0, 4 of 4096 18.3 |
+        // 19.1, 16 of 1229 24.2 | 23.5, one of 16384 23.0 | 24.2; d = 512, 8 samples of 4096 29.6 | 32.1, 16 of 1229 28.7 |
+        // 26.4; d = 1024, 8 of 8192 67.0 | 71.4, 4 of 4096 29.6 | 27.0, at T = 16 37.0 | 35.8 and 26.7 | 23.0; d = 2048, one
+        // sample of 8192 35.9 | 36.5, 12288 54.3 | 48.2, 16384 59.2 | 60.4, 32768 103.3 | 109.1, 8 of 4096 70.9 | 67.2.
         const int tblocks = ceil_div(T, kBfTokBlock);
         const long long groups = static_cast<long long>(n8) * tblocks * B;
-        const int slots = q.gate_blocks > kCUs ? 2 * kCUs : kCUs;  // pipelined workgroups per round (one sample)
-        const bool pipe = B == 1 && T <= kBfTokBlock && direct_ok &&
-                          16LL * q.gate_blocks >= 15LL * slots * ceil_div(q.gate_blocks, slots) &&
-                          !(q.gate_groups == 8 && slots == kCUs && s->d > 256 && s->d <= 1024);
-        if (groups >= 4 * kCUs && groups / 12 < (1 << 22) /* grid limit */ && !pipe) {
-            q.gate_tblocks = tblocks;
-            q.gate_nt = ceil_div(ceil_div(T, tblocks), 16);
-            long long best = -1;
+        if (groups >= 4 * kCUs && groups / 12 < (1 << 22) /* grid limit */) {
+            long long tile_cost = -1;
             for (int t = 1; t <= 12; ++t) {
                 const long long wgs = static_cast<long long>(ceil_div(n8, t)) * tblocks * B;
                 const long long cost = (wgs + kCUs - 1) / kCUs * (16 + t);
-                if (best < 0 || cost <= best) {
-                    best = cost;
+                if (tile_cost < 0 || cost <= tile_cost) {
+                    tile_cost = cost;
                     q.gate_tiles = t;
                 }
             }
-            q.gate_blocks = ceil_div(q.kcap / 8, q.gate_tiles);
+            const long long wgs = static_cast<long long>(q.gate_blocks) * B;
+            const int slots = wgs > kCUs ? 2 * kCUs : kCUs;
+            const long long full = (wgs + slots - 1) / slots;
+            const double rounds = full > 1 ? 0.5 * (static_cast<double>(wgs) / slots + full) : 1.0;
+            const double other_cost = rounds * (10 + q.gate_groups * (slots / kCUs)) * tblocks;
+            const bool pipe = direct_ok && T <= kBfTokBlock;
+            int tenths = 0;
+            if (s->d <= 256)
+                tenths = pipe && T > 16 ? 12 : 14;
+            else if (pipe && s->d <= 1024)
+                tenths = T > 32 ? 14 : 0;
+            else if (pipe)
+                tenths = B == 1 ? 13 : 0;
+            if (tenths > 0 && 10.0 * tile_cost > tenths * other_cost) {
+                q.gate_tiles = 0;
+            } else {
+                q.gate_tblocks = tblocks;
+                q.gate_nt = ceil_div(ceil_div(T, tblocks), 16);
+                q.gate_blocks = ceil_div(q.kcap / 8, q.gate_tiles);
+            }
         }
         q.col_tile = kBfColTile;
         q.ncol = ceil_div(s->d, q.col_tile);

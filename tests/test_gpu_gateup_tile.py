@@ -1,5 +1,5 @@
-"""The tiled gate/up kernel (calls with at least 1024 groups of 8 listed neurons over samples and token blocks) at the
-edges of its tiles and stages, against the float64 oracle within the bf16 bar, and Eq. 4 through it."""
+"""The tiled gate/up kernel (most calls with at least 1024 groups of 8 listed neurons over samples and token blocks) at the
+edges of its tiles and stages, and the calls of that size that the other kernels take, against the float64 oracle within the bf16 bar, and Eq. 4 through it."""
 import numpy as np
 import pytest
 import torch
@@ -23,13 +23,14 @@ CASES = [
     (2080, 800, 20, 12, 700, "random"), # more than 64 norm partials per row
     (64, 2600, 51, 8, 2561, "none"),    # one stage; lists of 81 chunks, 12 groups per workgroup
     (320, 9000, 5, 1, 8201, "ones"),    # one sample
-    # One sample at the pipelined kernel's widths, on both sides of the rule that chooses between the two.
+    # Calls of the same size on either side of the rule that chooses between the tiled kernel and the others.
     (256, 8300, 5, 1, 8192, "random"),    # pipelined, 256 workgroups of 4 groups
     (256, 8300, 5, 1, 8193, "random"),    # tiled (514 workgroups of 2)
-    (256, 15500, 3, 1, 15297, "none"),    # pipelined, 240 workgroups of 8
-    (256, 15500, 3, 1, 15296, "none"),    # tiled (239)
-    (512, 16400, 3, 1, 16384, "random"),  # tiled: one round of 8 groups over 2 chunks
-    (512, 31000, 2, 1, 30657, "none"),    # pipelined, 480 workgroups of 8, two per compute unit
+    (256, 4200, 20, 8, 4096, "none"),     # pipelined, 512 workgroups of 8, two per compute unit
+    (512, 8300, 33, 3, 8192, "random"),   # pipelined, 768 workgroups of 4, two per compute unit
+    (512, 8300, 32, 3, 8192, "random"),   # tiled: half of the pipelined kernel's 64 tokens
+    (512, 16400, 3, 1, 16384, "none"),    # tiled
+    (96, 4200, 130, 8, 4096, "ones"),     # staged, three token blocks
 ]
 
 
