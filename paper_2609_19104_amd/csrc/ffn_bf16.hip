@@ -21,7 +21,7 @@
 //                   staged in LDS in 256-column chunks (double-buffered) and shared by all NG groups, so each
 //                   byte of xn read from L2 serves NG times more neurons.
 //   gateup_tile:    many groups over samples and token blocks, see there.
-//   Both sum the d-split waves in LDS in a fixed order, then write h = SiLU(r g) * (r u) to H[t][slot] in
+//   All sum the d-split waves in LDS in a fixed order, then write h = act(r g) * (r u) to H (see h_at) in
 //   bf16.  Slots past the list get h = 0 so that the down projection can read whole 32-neuron chunks.
 //
 // down, 256 threads.  Workgroup = (64-column tile, K-slice of 32-neuron chunks, sample).  A = H (tokens x
@@ -633,7 +633,7 @@ __global__ __launch_bounds__(kGuThreads, (NG == 2 || kTwoPerCU) ? 4 : 2) void ga
 // flight.  Wave w takes K step w / 4 (32 columns) of every stage for tiles w % 4, w % 4 + 4, ..., so a stage's input
 // serves all tiles from LDS, and the two K halves are added through LDS.
 // What bounds it: 16 samples of 51 tokens, 1229 of 4096 neurons, d = 1024 (10 groups per workgroup, 256 workgroups, one
-// round) take 16.3 us, of which 9.8 are the launch, the indices', the first stages' round trips and the reduction, 5 the
+// round) take 16.5 us, of which 10 are the launch, the indices', the first stages' round trips and the reduction, 5 the
 // products and their barriers and under 2 waiting for later stages (timed without loads and without the loop).  The
 // pipelined kernel took 21.5: its weights go from memory to registers in fragment order, which the L1 looks up row by
 // row (6.6 M lookups, half of its time; 2.3 M here), and 624 workgroups ran in two rounds.

@@ -6,8 +6,8 @@
 // then carries the K values 4 g + j (j = 0..3) of a 16-wide step, in the same order for both operands, so a
 // 16-byte load feeds four calls and no lane permutation is needed.
 //
-// gate/up (gateup_f32_kernel), 512 threads = 8 waves, NG groups of 8 listed neurons x one block of up to 64 tokens.
-//   A = 8 gate + 8 up weight rows per group; B = the FFN input, NT tiles of 16 tokens.  The waves split d in units of
+// gate/up (gateup_f32_kernel), 512 threads = 8 waves, NG groups of 8 listed neurons x one block of up to 32 tokens.
+//   A = 8 gate + 8 up weight rows per group; B = the FFN input, NT (1 or 2) tiles of 16 tokens.  The waves split d in units of
 //   32 columns (a 128-byte line of every row), unit w, w + 8, ...: a wave copies a unit of the weight and token rows
 //   into its own LDS region, 8 lanes per line, and reads the fragments there.  (A fragment loaded straight from memory
 //   has 16 rows in 16 neighbouring lanes, and the L1 looks up a line per row and 16 lanes: 64 lookups for the kilobyte
@@ -31,7 +31,7 @@
 // to be used: a vector-ALU product of 8 tokens at a time, one wave per 8 neurons, read every weight 7 times.  One
 // layer of d = 1024, 1229 of 4096 neurons, 51 tokens, a norm: gate/up 136 -> 11.2 us (3.4 us of it matrix-core
 // work, 7.0 the launch, the first loads' two round trips and the sum over the waves), down and epilogue 44 -> 8 us;
-// the call 183 -> 18.5 us.  Four samples of it 296 -> 43 us.  More loads in flight per wave were slower in both
+// the call 183 -> 18.3 us.  Four samples of it 296 -> 43 us.  More loads in flight per wave were slower in both
 // kernels (that layer with one, two and three units ahead in gate/up: 19.0, 19.8, 20.1 us; with 6, 4 and 3 chunks
 // in the down kernel 19.0, 18.5, 18.2, but at 2 samples of d = 1568 41.0, 41.2, 42.9).
 #include <algorithm>

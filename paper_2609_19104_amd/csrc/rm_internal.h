@@ -88,7 +88,7 @@ struct Plan {
     int df_cw = 4;       // fused down: columns per lane (2 for one sample, 4 with several)
     int df_ncol = 0;     // fused down: column tiles of 16 df_cw columns
     int ntt = 0;         // fused down: token tiles of 16 df_nt tokens
-    int f32_nt = 4;      // f32 gate/up: 16-token tiles per token block
+    int f32_nt = 2;      // f32 gate/up: 16-token tiles per token block (1 or 2)
     int f32_tblocks = 1; // f32 gate/up: token blocks
     // bf16, one sample, d = 2048, the spread plan's list lengths, 256 compute units: gate/up and down in one
     // launch (layer_xcd_kernel) that reads the float32 input itself, slices = the 8 XCDs' slices of slice_units
