@@ -512,9 +512,9 @@ class ContextSetup:
 
     def hooks(self):  # matrix-core FLOPs of the two GEMMs over the recomputed rows
         rm, r = self.rm, self.rows_max
-        return [(rm.RM_KERNEL_GATEUP, "gate/up GEMM over the gathered rows (gemm_nt_kernel, GLU)", "gateup",
+        return [(rm.RM_KERNEL_GATEUP, "gate/up GEMM over the gathered rows (gemm_dma_kernel, GLU)", "gateup",
                  2 * projection_flops(r, self.d, self.d_ff)),
-                (rm.RM_KERNEL_DOWN, "down GEMM with the scatter (gemm_nt_kernel, scatter)", "down",
+                (rm.RM_KERNEL_DOWN, "down GEMM with the scatter (gemm_dma_kernel, scatter)", "down",
                  projection_flops(r, self.d, self.d_ff))]
 
 
