@@ -24,8 +24,8 @@
 // unit pulls tiles out of L2, not the matrix cores, so the tiles are as large as one workgroup per compute unit
 // allows: up to 256 rows by 128 columns of each weight matrix (2 MB read per gate/up workgroup over K = 2048), 8 waves,
 // K staged 64 wide (one cache line per row) straight from memory into LDS.  The rows are cut into equal tiles, so that
-// 390 rows take two tiles of 224 and not of 256: gate/up 76.1 -> 71.1 us, down 45.2 -> 43.9 (d = 2048, d_ff = 16384, one
-// box's trace); 144 rows one of 160: the layer 106.9 -> 92.1 us.  Tiles of 256 rows keep 4 waves along the rows x 2 along the columns
+// 390 rows take two tiles of 224 and not of 256: gate/up 76.1 -> 71.1 us, down 45.2 -> 43.9 (d = 2048, d_ff = 16384);
+// 144 rows one of 160: the layer 106.9 -> 92.1 us.  Tiles of 256 rows keep 4 waves along the rows x 2 along the columns
 // (2 x 4: 91.4 -> 94.6 us for 492 rows at d_ff = 2176).
 // Workgroups that share a weight tile are numbered onto one XCD so that its L2 serves the re-reads.
 #include <algorithm>
